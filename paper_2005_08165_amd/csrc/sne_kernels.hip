@@ -153,6 +153,18 @@ __device__ __forceinline__ float vmax3(float a, float b, float c) {
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
 }
+// x * y, and +0 if y is 0 whatever x is (infinities and NaN included): one
+// select of the factor y then blanks all products it enters.  Full rate.
+__device__ __forceinline__ float mul_or_zero(float x, float y) {
+    float r;
+    asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+__device__ __forceinline__ float neg_mul_or_zero(float x, float y) {  // -x * y
+    float r;
+    asm("v_mul_legacy_f32 %0, -%1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
 __device__ __forceinline__ float vmed3(float a, float b, float c) {
     float r;
     asm("v_med3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
@@ -164,20 +176,41 @@ __device__ __forceinline__ float vmed3(float a, float b, float c) {
 template <int KIND> struct Raw;
 template <> struct Raw<KIND_F32> {
     using T = float;
-    __device__ static float value(T x) { return __builtin_amdgcn_classf(x, kPosFinite) ? x : 0.f; }
+    __device__ static bool ok(T x) { return __builtin_amdgcn_classf(x, kPosFinite); }
+    __device__ static float value(T x) { return ok(x) ? x : 0.f; }
+    // in the register window samples stay as they are, valid or not: masks
+    // say which are (see Mask)
+    __device__ static float window(T x) { return x; }
 };
 template <> struct Raw<KIND_DISP> : Raw<KIND_F32> {};
 template <> struct Raw<KIND_U16> {
     using T = uint16_t;
+    __device__ static bool ok(T x) { return x != 0; }
     __device__ static float value(T x) { return (float)x; }  // 0 = invalid
+    __device__ static float window(T x) { return (float)x; }
 };
 template <> struct Raw<KIND_F16> {
     using T = uint16_t;  // binary16 bits
-    __device__ static float value(T x) {
-        const float f = (float)__builtin_bit_cast(_Float16, x);
-        return __builtin_amdgcn_classf(f, kPosFinite) ? f : 0.f;
-    }
+    __device__ static float window(T x) { return (float)__builtin_bit_cast(_Float16, x); }
+    __device__ static bool ok(T x) { return __builtin_amdgcn_classf(window(x), kPosFinite); }
+    __device__ static float value(T x) { return ok(x) ? window(x) : 0.f; }
 };
+
+// One bit per lane.  (The predicate `lane` makes of a mask is used from a
+// variable: inside a conditional operator it would become a branch.)
+// Validity is kept as such masks in scalar registers: a
+// window's validity is a few scalar ands, which issue beside the vector
+// instructions of other wavefronts, instead of minima over the nine samples
+// and a compare per pixel, and holds no vector registers.  Together with one
+// select per pixel for the three channels (mul_or_zero) and the middle row's
+// pairs formed last, this took the 4-column FP32 Sobel-median kernel from
+// 127 to 114 registers and 48 to 40 half-rate instructions per pixel:
+// 64 x 480x640 in 57.6 instead of 60.4 us (5.8 TB/s of algorithmic bytes,
+// about what the plain streams of its access pattern reach), 1024 uneven u16
+// frames FD-mean in 1.91 instead of 2.0 ms.
+using Mask = uint64_t;
+__device__ __forceinline__ Mask mask_of(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ bool lane(Mask m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 template <typename T, int N> struct alignas(sizeof(T) * N) Vec { T v[N]; };
 
@@ -245,16 +278,17 @@ __device__ __forceinline__ void load_raw(const InBuf &b, int r, int col_off, int
 // Per-row state.  Index i of z/s is column (lane base + i - 1): 0 and PX+1
 // are the neighbours from the adjacent lanes.
 template <int PX> struct Row {
-    float z[PX + 2];   // raw value (0 where invalid)
+    float z[PX + 2];   // raw value (Raw::window)
     float s[PX + 2];   // filtered image
-    float hmin[PX];    // min z over columns k-1..k+1: > 0 iff all 3 valid
     float D[PX];       // s[k+1] - s[k-1] (horizontal central difference)
     float rE[PX + 1];  // rE[i] = 1 / (z[i+1] - z[i])
+    Mask ok[PX + 2];   // sample valid
+    Mask hok[PX];      // columns k-1..k+1 valid
     // lenient rule with a 3-row filter only: the row's horizontal gradient
     // line at columns 1..PX and whether it has one (computed once, used by
     // the three output rows whose window holds this row)
     float Lh[PX];
-    bool hh[PX];
+    Mask hh[PX];
 };
 
 // Lanes at the inner edges of two half-wave tiles (31 and 32) take their
@@ -277,34 +311,57 @@ __device__ __forceinline__ float right_of(float old, float src, const Edges &e) 
     return v;
 }
 
-template <int KIND, int PX, bool HALF>
-__device__ __forceinline__ void finish_row(const RawRow<KIND, PX> &raw, Row<PX> &o,
-                                           const Edges &e) {
-    const float h = Raw<KIND>::value(raw.h);
-#pragma unroll
-    for (int k = 0; k < PX; ++k) o.z[k + 1] = Raw<KIND>::value(raw.x.v[k]);
-    o.z[0] = left_of<HALF>(h, o.z[PX], e);
-    o.z[PX + 1] = right_of<HALF>(h, o.z[1], e);
-    if constexpr (KIND == KIND_DISP) {
-#pragma unroll
-        for (int i = 0; i < PX + 2; ++i) o.s[i] = o.z[i];
-    } else {
-        const float hs = rcp(h);
-#pragma unroll
-        for (int k = 1; k <= PX; ++k) o.s[k] = rcp(o.z[k]);
-        o.s[0] = left_of<HALF>(hs, o.s[PX], e);
-        o.s[PX + 1] = right_of<HALF>(hs, o.s[1], e);
-    }
+// Quantised raw values (uint16, binary16) repeat along iso-depth lines so
+// often that nearly every wavefront holds a pixel with a left-out neighbour:
+// those kinds take the general aggregation everywhere, without the per-pixel
+// test and wavefront vote that let the FP32 kinds skip it.  With no branch the compiler also shares
+// a pair's equality test between the two pixels of the pair.
+template <int KIND> constexpr bool kTieHeavy = KIND == KIND_U16 || KIND == KIND_F16;
+
+// s[k+1] - s[k-1] at the lane's columns.
+template <int KIND, int PX> __device__ __forceinline__ void make_hdiff(Row<PX> &o) {
 #pragma unroll
     for (int k = 0; k < PX; ++k) {
-        o.hmin[k] = vmin3(o.z[k], o.z[k + 1], o.z[k + 2]);
         if constexpr (KIND == KIND_DISP)
             o.D[k] = o.z[k + 2] - o.z[k];
         else
             o.D[k] = (o.z[k] - o.z[k + 2]) * (o.s[k] * o.s[k + 2]);
     }
+}
+
+// A row's values and validity, and for the 3-row filters its horizontal
+// differences (FD needs only those of the middle row: make_middle).
+template <int KIND, int PX, bool HALF, bool FD>
+__device__ __forceinline__ void finish_row(const RawRow<KIND, PX> &raw, Row<PX> &o,
+                                           const Edges &e) {
+    // lanes that take their outer neighbour from the halo sample
+    constexpr Mask kLeft = HALF ? 0x100000001ull : 1ull, kRight = kLeft << (HALF ? 31 : 63);
+    const float h = Raw<KIND>::window(raw.h);
+    const Mask okh = mask_of(Raw<KIND>::ok(raw.h));
+#pragma unroll
+    for (int k = 0; k < PX; ++k) {
+        o.z[k + 1] = Raw<KIND>::window(raw.x.v[k]);
+        o.ok[k + 1] = mask_of(Raw<KIND>::ok(raw.x.v[k]));
+    }
+    o.z[0] = left_of<HALF>(h, o.z[PX], e);
+    o.z[PX + 1] = right_of<HALF>(h, o.z[1], e);
+    o.ok[0] = ((o.ok[PX] << 1) & ~kLeft) | (okh & kLeft);
+    o.ok[PX + 1] = ((o.ok[1] >> 1) & ~kRight) | (okh & kRight);
+#pragma unroll
+    for (int k = 0; k < PX; ++k) o.hok[k] = o.ok[k] & o.ok[k + 1] & o.ok[k + 2];
+    // the outer columns' reciprocals are formed again: one v_rcp each costs
+    // less than the lane shift and the half-wave select
+#pragma unroll
+    for (int i = 0; i < PX + 2; ++i) o.s[i] = KIND == KIND_DISP ? o.z[i] : rcp(o.z[i]);
+    if constexpr (!FD) make_hdiff<KIND, PX>(o);
+}
+
+// What only the middle row of the window needs, formed when a row becomes
+// that (earlier it would hold registers): the horizontal pairs.
+template <int KIND, int PX, bool FD> __device__ __forceinline__ void make_middle(Row<PX> &o) {
 #pragma unroll
     for (int i = 0; i <= PX; ++i) o.rE[i] = rcp(o.z[i + 1] - o.z[i]);
+    if constexpr (FD) make_hdiff<KIND, PX>(o);
 }
 
 // Reciprocals of the vertical and diagonal pairs between an upper row and the
@@ -382,10 +439,12 @@ template <int PX> struct RowState {
     Pairs<PX> below;
 };
 
-__device__ __forceinline__ float median_pair(float (&t)[8], bool odd) {
+// B + the median: 0.5 (x3 + x4), x3 alone if an odd number of values is kept
+// (halving is exact, so the fused form rounds once like B + median).
+__device__ __forceinline__ float median_pair(const float (&t)[8], bool odd, float B) {
     float x3, x4;
     middle_pair(t, x3, x4);
-    return odd ? x3 : 0.5f * (x3 + x4);
+    return fmaf(0.5f, x3 + (odd ? x3 : x4), B);
 }
 
 // Candidates t_j = N_j w_j of the 8 slots (see the file header).  Called
@@ -404,68 +463,58 @@ __device__ __forceinline__ void candidates(const float (&Nj)[8], const float (&r
     }
 }
 
-// Median of the kept candidates; zj/zc decide which slots are left out.
+// B + the median of the kept candidates; zj/zc decide which slots are left out.
 // `general` pads left-out slots alternately +inf / -inf; otherwise all 8
 // are kept.  With nothing kept, the four +inf and four -inf pads give
 // -inf + inf = NaN, which the caller's norm test turns into the degenerate
 // normal.
 // A neighbour gives no candidate when its raw value equals the centre's
-// (dZ = 0) or, under the lenient rule, when it is invalid (read as 0).
-template <bool LEN> __device__ __forceinline__ bool left_out(float zj, float zc) {
-    if constexpr (LEN) return zj == zc || zj == 0.f;
+// (dZ = 0) or, under the lenient rule, when it is invalid.
+template <bool LEN> __device__ __forceinline__ bool left_out(float zj, float zc, Mask okj) {
+    if constexpr (LEN) return lane(mask_of(zj == zc) | ~okj);
     return zj == zc;
 }
 
 template <int KIND, bool LEN>
 __device__ __forceinline__ float median8(const float (&Nj)[8], const float (&rj)[8],
-                                         const float (&zj)[8], float zc, bool general) {
+                                         const float (&zj)[8], const Mask (&okj)[8], float zc, float B, bool general) {
     float t[8];
-    if (!general) {
-        candidates<KIND>(Nj, rj, zc, t);
-        return median_pair(t, false);
-    }
     candidates<KIND>(Nj, rj, zc, t);
+    if (!general) return median_pair(t, false, B);
     float pad = kInf;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const bool drop = left_out<LEN>(zj[j], zc);
+        const bool drop = left_out<LEN>(zj[j], zc, okj[j]);
         t[j] = drop ? pad : t[j];
         pad = drop ? -pad : pad;
     }
-    return median_pair(t, pad < 0.f);  // odd number left out -> position 3
+    return median_pair(t, pad < 0.f, B);  // odd number left out -> position 3
 }
 
-// Mean of the kept candidates.  Both paths add in the same tree order and
-// 1/8 is exact, so a pixel with nothing left out gets the same bits whichever
-// path its wavefront takes.  With nothing kept the sum is +0 and 0 * (1/0)
-// is NaN, which the caller's norm test turns into the degenerate normal.
+// B + the mean of the kept candidates.  Both paths add in the same tree
+// order, 1/8 is exact and v_rcp_f32 returns it exactly for m = 8, so a pixel
+// with nothing left out gets the same bits whichever path its wavefront
+// takes.  With nothing kept the sum is +0 and 0 * (1/0) is NaN, which the
+// caller's norm test turns into the degenerate normal.
 template <int KIND, bool LEN>
 __device__ __forceinline__ float mean8(const float (&Nj)[8], const float (&rj)[8],
-                                       const float (&zj)[8], float zc, bool general) {
+                                       const float (&zj)[8], const Mask (&okj)[8], float zc, float B, bool general) {
     float t[8];
     candidates<KIND>(Nj, rj, zc, t);
-    if (!general) {
-        const float s = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-        return s * 0.125f;
-    }
-    int m = 0;
+    float w = 0.125f;
+    if (general) {
+        int m = 0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const bool drop = left_out<LEN>(zj[j], zc);
-        t[j] = drop ? 0.f : t[j];
-        m += drop ? 0 : 1;
+        for (int j = 0; j < 8; ++j) {
+            const bool drop = left_out<LEN>(zj[j], zc, okj[j]);
+            t[j] = drop ? 0.f : t[j];
+            m += drop ? 0 : 1;
+        }
+        w = rcp((float)m);
     }
     const float s = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-    return s * rcp((float)m);  // v_rcp_f32 returns 1/8 exactly for m = 8
+    return fmaf(s, w, B);
 }
-
-// Integer raw values (uint16) repeat along iso-depth lines so often that
-// nearly every wavefront holds a pixel with a left-out neighbour: those
-// kinds take the general aggregation everywhere, without the per-pixel test
-// and wavefront vote that let the other kinds skip it.  With no branch the
-// compiler also shares a pair's equality test between the two pixels of the
-// pair.
-template <int KIND> constexpr bool kTieHeavy = KIND == KIND_U16;
 
 // Outputs are written once and not read back by this kernel: nontemporal
 // stores keep them from displacing the input rows that neighbouring tiles
@@ -505,8 +554,8 @@ __device__ __forceinline__ float one_sided(float za, float zb, float sa, float s
 // Returns the line's difference (0 if it has none) and sets `have`.
 template <int KIND>
 __device__ __forceinline__ float lenient_line(float zm, float z0, float zp, float sm, float s0,
-                                              float sp, float both, bool &have) {
-    const bool okm = zm > 0.f, ok0 = z0 > 0.f, okp = zp > 0.f;
+                                              float sp, float both, Mask okm, Mask ok0, Mask okp,
+                                              Mask &have) {
     float plus, minus;  // one-sided: 2 (sp - s0) and 2 (s0 - sm)
     if constexpr (KIND == KIND_DISP) {
         plus = 2.f * (zp - z0);
@@ -515,8 +564,11 @@ __device__ __forceinline__ float lenient_line(float zm, float z0, float zp, floa
         plus = 2.f * ((z0 - zp) * (s0 * sp));
         minus = 2.f * ((zm - z0) * (sm * s0));
     }
-    have = (okm && okp) || (ok0 && (okm || okp));
-    return (okm && okp) ? both : (ok0 && okp) ? plus : (ok0 && okm) ? minus : 0.f;
+    have = (okm & okp) | (ok0 & (okm | okp));
+    const bool two = lane(okm & okp), any = lane(have), up = lane(okp);
+    const float one = up ? plus : minus;
+    const float some = any ? one : 0.f;
+    return two ? both : some;
 }
 
 // The lenient horizontal lines of a finished row.
@@ -524,26 +576,45 @@ template <int KIND, int PX> __device__ __forceinline__ void lenient_hlines(Row<P
 #pragma unroll
     for (int k = 0; k < PX; ++k)
         o.Lh[k] = lenient_line<KIND>(o.z[k], o.z[k + 1], o.z[k + 2], o.s[k], o.s[k + 1],
-                                     o.s[k + 2], o.D[k], o.hh[k]);
+                                     o.s[k + 2], o.D[k], o.ok[k], o.ok[k + 1], o.ok[k + 2],
+                                     o.hh[k]);
 }
 
 // Lenient G from its lines (centre line c, side lines a and b, each 0 when
 // missing): the strict combination of the available lines, rescaled to the
 // full filter's weight.  With every line present it is the strict value.
-template <bool FD>
-__device__ __forceinline__ float lenient_combine(float c, bool hc, float a, bool ha, float b,
-                                                 bool hb, const GradW &w, bool &have) {
-    if constexpr (FD) {
-        have = hc;
-        return c;
-    } else {
-        const float g = fmaf(w.wa, a + b, c);
-        const int sides = (ha ? 1 : 0) + (hb ? 1 : 0);
-        have = hc || sides > 0;
-        const float scale = hc ? (sides == 2 ? 1.f : sides == 1 ? w.r[0] : w.r[1])
-                               : (sides == 2 ? w.r[2] : w.r[3]);
-        return g * scale;
-    }
+__device__ __forceinline__ float lenient_combine(float c, Mask hc, float a, Mask ha, float b,
+                                                 Mask hb, const GradW &w, Mask &have) {
+    const float g = fmaf(w.wa, a + b, c);
+    const Mask both = ha & hb, any = ha | hb;
+    have = hc | any;
+    const bool centre = lane(hc), two = lane(both), some = lane(any);
+    const float with_side = some ? w.r[0] : w.r[1];
+    const float with = two ? 1.f : with_side, without = two ? w.r[2] : w.r[3];
+    return g * (centre ? with : without);
+}
+
+// n_z of column k of the middle row: B + Phi over the 8 slots.
+template <int KIND, int AGG, bool LEN, bool GENERAL, int PX>
+__device__ __forceinline__ float normal_z(int k, const FrameDesc &f, int col, float fv, float Gu,
+                                          float Gv, const Row<PX> &rp, const Row<PX> &rc,
+                                          const Row<PX> &rn, const Pairs<PX> &pu,
+                                          const Pairs<PX> &pd) {
+    const int c = k + 1;
+    const float zc = rc.z[c];
+    const float fu = (float)(col + k) - f.u0;
+    const float B = fmaf(fu, Gu, fv * Gv);
+    const float Spp = Gu + Gv, Spm = Gu - Gv;
+    // slots: E, W, S, N, SE, NW, SW, NE
+    const float zj[8] = {rc.z[c + 1], rc.z[c - 1], rn.z[c], rp.z[c],
+                         rn.z[c + 1], rp.z[c - 1], rn.z[c - 1], rp.z[c + 1]};
+    const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};
+    const float rj[8] = {rc.rE[c], -rc.rE[c - 1], pd.rS[k], -pu.rS[k],
+                         pd.rSE[c], -pu.rSE[k], pd.rSW[k], -pu.rSW[c]};
+    const Mask okj[8] = {rc.ok[c + 1], rc.ok[c - 1], rn.ok[c],     rp.ok[c],
+                         rn.ok[c + 1], rp.ok[c - 1], rn.ok[c - 1], rp.ok[c + 1]};
+    return (AGG == AGG_MEAN) ? mean8<KIND, LEN>(Nj, rj, zj, okj, zc, B, GENERAL)
+                             : median8<KIND, LEN>(Nj, rj, zj, okj, zc, B, GENERAL);
 }
 
 // Output row r of a tile from the window (prev, cur, next); `pend` holds the
@@ -557,7 +628,7 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
                                          RowState<PX> &next) {
     constexpr bool FD = GK == GK_FD;
     constexpr bool LENR = LEN && GK != GK_CUSTOM;  // the lenient rule applies
-    finish_row<KIND, PX, HALF>(pend, next.row, e);
+    finish_row<KIND, PX, HALF, FD>(pend, next.row, e);
     if constexpr (LENR && !FD) lenient_hlines<KIND, PX>(next.row);
     load_raw<KIND, PX>(ib, r + 1 + SNE_PREFETCH_ROWS, col_off, halo_off, pend);  // prefetch
     // packed output: this row's RGBX bytes, in flight while the row is
@@ -567,6 +638,7 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
         rgbx = buf_load<float, PX>(
             rgbb, (int)((unsigned)r * (unsigned)rgbb.pitch_bytes + (unsigned)(col_off < kOOB
                                                                              ? col * 4 : kOOB)));
+    make_middle<KIND, PX, FD>(cur.row);
     make_pairs<PX>(cur.row, next.row, cur.below);
     const Row<PX> &rp = prev.row, &rc = cur.row, &rn = next.row;
     const Pairs<PX> &pu = prev.below, &pd = cur.below;
@@ -589,121 +661,138 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
     // (each used by three pixels; the horizontal ones come with the rows)
     bool lenient_path = false;
     float VL[PX + 2];
-    bool VH[PX + 2];
+    Mask VH[PX + 2];
     if constexpr (LENR && !FD) {
-        bool need = false;
+        Mask need = 0;
 #pragma unroll
         for (int k = 0; k < PX; ++k)
-            need = need ||
-                   (!(vmin3(rp.hmin[k], rc.hmin[k], rn.hmin[k]) > 0.f) && rc.z[k + 1] > 0.f);
-        if (__builtin_amdgcn_ballot_w64(need) != 0) {
+            need |= rc.ok[k + 1] & ~(rp.hok[k] & rc.hok[k] & rn.hok[k]);
+        if (need != 0) {
             lenient_path = true;
 #pragma unroll
             for (int i = 0; i < PX + 2; ++i)
                 VL[i] = lenient_line<KIND>(rp.z[i], rc.z[i], rn.z[i], rp.s[i], rc.s[i], rn.s[i],
-                                           V[i], VH[i]);
+                                           V[i], rp.ok[i], rc.ok[i], rn.ok[i], VH[i]);
         }
     }
 
-    using OT = typename Out<OUT>::T;
-    Vec<OT, PX> ox, oy, oz;
-    uint8_t mk[PX];
-    const float fv = (float)r - f.v0;
+    // pixels that take the general aggregation whatever the vote below says
+    bool general[PX];
+#pragma unroll
+    for (int k = 0; k < PX; ++k) general[k] = kTieHeavy<KIND>;
+
+    float Gu[PX], Gv[PX];
+    Mask valid[PX];
 #pragma unroll
     for (int k = 0; k < PX; ++k) {
         const int c = k + 1;
-        const float zc = rc.z[c];
-        bool valid = vmin3(rp.hmin[k], rc.hmin[k], rn.hmin[k]) > 0.f;
-        float Gu, Gv;
+        valid[k] = rp.hok[k] & rc.hok[k] & rn.hok[k];
         if constexpr (FD) {
-            Gu = rc.D[k];
-            Gv = V[c];
+            Gu[k] = rc.D[k];
+            Gv[k] = V[c];
         } else if constexpr (GK == GK_CUSTOM) {
             // any 3x3 K_x: per line k2 (s_+ - s_0) - k0 (s_0 - s_-) + ks s_0;
             // line a of K_y (column c + a - 1) is row a of K_x
-            Gu = 0.f;
-            Gv = 0.f;
+            Gu[k] = 0.f;
+            Gv[k] = 0.f;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const Row<PX> &X = a == 0 ? rp : (a == 1 ? rc : rn);
                 const float hp = one_sided<KIND>(X.z[c], X.z[c + 1], X.s[c], X.s[c + 1]);
                 const float hm = one_sided<KIND>(X.z[c - 1], X.z[c], X.s[c - 1], X.s[c]);
-                Gu += fmaf(gw.k2[a], hp, fmaf(-gw.k0[a], hm, gw.ks[a] * X.s[c]));
+                Gu[k] += fmaf(gw.k2[a], hp, fmaf(-gw.k0[a], hm, gw.ks[a] * X.s[c]));
                 const int b = c + a - 1;
                 const float vp = one_sided<KIND>(rc.z[b], rn.z[b], rc.s[b], rn.s[b]);
                 const float vm = one_sided<KIND>(rp.z[b], rc.z[b], rp.s[b], rc.s[b]);
-                Gv += fmaf(gw.k2[a], vp, fmaf(-gw.k0[a], vm, gw.ks[a] * rc.s[b]));
+                Gv[k] += fmaf(gw.k2[a], vp, fmaf(-gw.k0[a], vm, gw.ks[a] * rc.s[b]));
             }
         } else {
             // the 3-row filter divided by its centre weight (wa = side /
             // centre): n' scales as a whole, the normal does not change
-            Gu = fmaf(gw.wa, rp.D[k] + rn.D[k], rc.D[k]);
-            Gv = fmaf(gw.wa, V[c - 1] + V[c + 1], V[c]);
+            Gu[k] = fmaf(gw.wa, rp.D[k] + rn.D[k], rc.D[k]);
+            Gv[k] = fmaf(gw.wa, V[c - 1] + V[c + 1], V[c]);
         }
         // with every line present the lenient G is the strict one, bit for
         // bit, so pixels with a full window may take either path
         if constexpr (LENR && FD) {
             // FD has one line per direction: decided per column position,
             // nothing shared
-            if (__builtin_amdgcn_ballot_w64(!valid && zc > 0.f) != 0) {
-                lenient_path = true;
-                bool hc, vc;
-                const float Lc = lenient_line<KIND>(rc.z[c - 1], zc, rc.z[c + 1], rc.s[c - 1],
-                                                    rc.s[c], rc.s[c + 1], rc.D[k], hc);
-                const float Vc = lenient_line<KIND>(rp.z[c], zc, rn.z[c], rp.s[c], rc.s[c],
-                                                    rn.s[c], V[c], vc);
-                Gu = Lc;
-                Gv = Vc;
-                valid = zc > 0.f && hc && vc;
-            } else {
-                lenient_path = false;
+            if ((rc.ok[c] & ~valid[k]) != 0) {
+                general[k] = true;
+                Mask hc, vc;
+                Gu[k] = lenient_line<KIND>(rc.z[c - 1], rc.z[c], rc.z[c + 1], rc.s[c - 1],
+                                           rc.s[c], rc.s[c + 1], rc.D[k], rc.ok[c - 1], rc.ok[c],
+                                           rc.ok[c + 1], hc);
+                Gv[k] = lenient_line<KIND>(rp.z[c], rc.z[c], rn.z[c], rp.s[c], rc.s[c], rn.s[c],
+                                           V[c], rp.ok[c], rc.ok[c], rn.ok[c], vc);
+                valid[k] = rc.ok[c] & hc & vc;
             }
         } else if constexpr (LENR) {
             if (lenient_path) {
-                bool du, dv;
-                Gu = lenient_combine<FD>(rc.Lh[k], rc.hh[k], rp.Lh[k], rp.hh[k], rn.Lh[k],
-                                         rn.hh[k], gw, du);
-                Gv = lenient_combine<FD>(VL[c], VH[c], VL[c - 1], VH[c - 1], VL[c + 1],
-                                         VH[c + 1], gw, dv);
-                valid = zc > 0.f && du && dv;
+                general[k] = true;
+                Mask du, dv;
+                Gu[k] = lenient_combine(rc.Lh[k], rc.hh[k], rp.Lh[k], rp.hh[k], rn.Lh[k],
+                                        rn.hh[k], gw, du);
+                Gv[k] = lenient_combine(VL[c], VH[c], VL[c - 1], VH[c - 1], VL[c + 1],
+                                        VH[c + 1], gw, dv);
+                valid[k] = rc.ok[c] & du & dv;
             }
         }
-        const float fu = (float)(col + k) - f.u0;
-        const float B = fmaf(fu, Gu, fv * Gv);
-        const float Spp = Gu + Gv, Spm = Gu - Gv;
-        // slots: E, W, S, N, SE, NW, SW, NE
-        const float zj[8] = {rc.z[c + 1], rc.z[c - 1], rn.z[c], rp.z[c],
-                             rn.z[c + 1], rp.z[c - 1], rn.z[c - 1], rp.z[c + 1]};
-        const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};
-        const float rj[8] = {rc.rE[c], -rc.rE[c - 1], pd.rS[k], -pu.rS[k],
-                             pd.rSE[c], -pu.rSE[k], pd.rSW[k], -pu.rSW[c]};
+    }
+    const float fv = (float)r - f.v0;
+    float nz[PX];
+#pragma unroll
+    for (int k = 0; k < PX; ++k) {
         // A slot is left out iff raw_j == raw, i.e. its pair reciprocal is
-        // +-inf.  That is rare in float data: pad only when a valid pixel of
+        // +-inf.  That is rare in FP32 data: pad only when a valid pixel of
         // this wavefront needs it (the choice is wave-uniform, and both paths
         // give the same result when nothing is left out).
         // (signs do not matter here: the raw pair values are used)
-        bool general = true;
         if constexpr (!kTieHeavy<KIND>) {
-            if (!lenient_path) {
-                const float rmax = vmax8abs(rc.rE[c], rc.rE[c - 1], pd.rS[k], pu.rS[k],
-                                            pd.rSE[c], pu.rSE[k], pd.rSW[k], pu.rSW[c]);
-                const bool any_drop = !(rmax < kInf);
-                general = __builtin_amdgcn_ballot_w64(valid && any_drop) != 0;
-            }
+            const int c = k + 1;
+            const float rmax = vmax8abs(rc.rE[c], rc.rE[c - 1], pd.rS[k], pu.rS[k], pd.rSE[c],
+                                        pu.rSE[k], pd.rSW[k], pu.rSW[c]);
+            general[k] = general[k] || (mask_of(rmax == kInf) & valid[k]) != 0;
         }
-        const float phi = (AGG == AGG_MEAN) ? mean8<KIND, LEN>(Nj, rj, zj, zc, general)
-                                            : median8<KIND, LEN>(Nj, rj, zj, zc, general);
-        const float nx = f.fx * Gu, ny = f.fy * Gv, nz = B + phi;
-        const float n2 = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
-        // nothing kept (phi NaN) or a zero vector: the degenerate normal
-        const bool deg = !(n2 > 0.f);
-        const float inv = __builtin_amdgcn_rsqf(n2);
-        const bool keep = valid && !deg;
-        ox.v[k] = Out<OUT>::cvt(keep ? -nx * inv : 0.f);
-        oy.v[k] = Out<OUT>::cvt(keep ? -ny * inv : 0.f);
-        oz.v[k] = Out<OUT>::cvt(keep ? nz * inv : (valid ? -1.f : 0.f));
-        mk[k] = valid ? 1 : 0;
+        if (general[k])
+            nz[k] = normal_z<KIND, AGG, LEN, true, PX>(k, f, col, fv, Gu[k], Gv[k], rp, rc, rn, pu,
+                                                       pd);
+        else
+            nz[k] = normal_z<KIND, AGG, LEN, false, PX>(k, f, col, fv, Gu[k], Gv[k], rp, rc, rn,
+                                                        pu, pd);
     }
+
+    using OT = typename Out<OUT>::T;
+    Vec<OT, PX> ox, oy, oz;
+    bool mk[PX];
+    float fz[PX];
+    Mask deg[PX], any_deg = 0;
+#pragma unroll
+    for (int k = 0; k < PX; ++k) {
+        const float nx = f.fx * Gu[k], ny = f.fy * Gv[k];
+        const float n2 = fmaf(nx, nx, fmaf(ny, ny, nz[k] * nz[k]));
+        // n2 is NaN where nothing was kept and 0 for a zero vector: there the
+        // normal is (0, 0, -1), set below for the few rows that hold one
+        const Mask pos = mask_of(n2 > 0.f);
+        deg[k] = valid[k] & ~pos;
+        any_deg |= deg[k];
+        const bool keep = lane(valid[k] & pos);
+        const float rs = __builtin_amdgcn_rsqf(n2);
+        const float inv = keep ? rs : 0.f;
+        ox.v[k] = Out<OUT>::cvt(neg_mul_or_zero(nx, inv));
+        oy.v[k] = Out<OUT>::cvt(neg_mul_or_zero(ny, inv));
+        fz[k] = mul_or_zero(nz[k], inv);
+        mk[k] = lane(valid[k]);
+    }
+    if (any_deg != 0) {
+#pragma unroll
+        for (int k = 0; k < PX; ++k) {
+            const bool d = lane(deg[k]);
+            fz[k] = d ? -1.f : fz[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < PX; ++k) oz.v[k] = Out<OUT>::cvt(fz[k]);
     if constexpr (OUT == OUT_RGBN) {
         // one 16-byte pixel: R, G, B (bytes / 255), mask, n_x, n_y, n_z, 0
         if (col < f.W && r < rend) {
@@ -781,9 +870,9 @@ __device__ __forceinline__ void run_tile(const FrameDesc &f, int c0, int r0, int
     RawRow<KIND, PX> p0;
     RowState<PX> A, B, C;
     load_raw<KIND, PX>(ib, rb - 1, col_off, halo_off, p0);
-    finish_row<KIND, PX, HALF>(p0, A.row, e);
+    finish_row<KIND, PX, HALF, GK == GK_FD>(p0, A.row, e);
     load_raw<KIND, PX>(ib, rb, col_off, halo_off, p0);
-    finish_row<KIND, PX, HALF>(p0, B.row, e);
+    finish_row<KIND, PX, HALF, GK == GK_FD>(p0, B.row, e);
     if constexpr (LEN && GK == GK_3ROW) {  // the lenient rule's shared horizontal lines
         lenient_hlines<KIND, PX>(A.row);
         lenient_hlines<KIND, PX>(B.row);
@@ -1018,9 +1107,10 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
             const float rmax = vmax8abs(rj[0], rj[1], rj[2], rj[3], rj[4], rj[5], rj[6], rj[7]);
             general = __builtin_amdgcn_ballot_w64(valid && !(rmax < kInf)) != 0;
         }
-        const float phi = (AGG == AGG_MEAN) ? mean8<KIND, false>(Nj, rj, zj, z0, general)
-                                            : median8<KIND, false>(Nj, rj, zj, z0, general);
-        const float nx = f.fx * Gu, ny = f.fy * Gv, nz = B + phi;
+        const Mask okj[8] = {};  // strict rule: not looked at
+        const float nz = (AGG == AGG_MEAN) ? mean8<KIND, false>(Nj, rj, zj, okj, z0, B, general)
+                                           : median8<KIND, false>(Nj, rj, zj, okj, z0, B, general);
+        const float nx = f.fx * Gu, ny = f.fy * Gv;
         const float n2 = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
         const bool deg = !(n2 > 0.f);
         const float inv = __builtin_amdgcn_rsqf(n2);

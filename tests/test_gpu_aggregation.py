@@ -49,3 +49,40 @@ def test_every_number_of_kept_candidates(kind, agg):
             on, om = oracle.estimate(img, ORACLE_KIND[kind], k32(K), "fd", agg)
             check_parity(n.double().cpu().numpy(), m.cpu().numpy(), on, om,
                          label="%s %s %d values %dx%d" % (kind, agg, values, H, W))
+
+
+def _noisy(kind, H, W):
+    """A slanted surface with noise and 25 % invalid samples of every sort."""
+    rng = np.random.default_rng(9200)
+    z = 1.5 + np.arange(W) / W + 0.4 * np.arange(H)[:, None] / H + 0.01 * rng.standard_normal((H, W))
+    z = z * (1000.0 if kind == "depth_u16" else 20.0 if kind == "disparity_f32" else 1.0)
+    z = z.astype(DTYPE[kind])
+    bad = rng.random((H, W))
+    z[bad < 0.25] = 0
+    if kind != "depth_u16":
+        for i, v in enumerate((np.nan, np.inf, -np.inf, -1.0, -0.0)):
+            z[(bad >= 0.01 * i) & (bad < 0.01 * i + 0.01)] = v
+    return z
+
+
+@pytest.mark.parametrize("rule", ["strict", "lenient"])
+@pytest.mark.parametrize("kind", list(DTYPE))
+def test_validity_across_lane_and_tile_edges(kind, rule):
+    """Holes on both sides of every boundary between lanes, half waves and
+    tiles: each tile shape against the oracle."""
+    H, W, K = 23, 516, (400.0, 400.0, 255.5, 12.0)
+    img = _noisy(kind, H, W)
+    dev = torch.from_numpy(img).cuda()
+    ctx = sne.Context(0, tuning=False)
+    suffix = "+lenient" if rule == "lenient" else ""
+    # quantised depth: FD only (see above)
+    second = "fd" if kind in ("depth_u16", "depth_f16") else "sobel"
+    for grad, agg in (("fd", "mean"), (second, "median")):
+        on, om = oracle.estimate(img, ORACLE_KIND[kind], k32(K), grad, agg, rule=rule)
+        assert 0.01 < om.mean() < (0.95 if suffix else 0.2)
+        for px, rows, lanes in ((1, 1, 64), (1, 5, 32), (2, 3, 64), (2, 4, 32), (4, 5, 64),
+                                (4, 4, 32)):
+            ctx.set_tile(px, rows, lanes)
+            n, m = sne.estimate(dev, K, kind + suffix, grad, agg, ctx=ctx)
+            check_parity(n.double().cpu().numpy(), m.cpu().numpy(), on, om,
+                         label="%s %s-%s tile %dx%d/%d" % (kind + suffix, grad, agg, px, rows, lanes))
