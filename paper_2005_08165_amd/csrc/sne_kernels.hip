@@ -284,6 +284,7 @@ template <int PX> struct Row {
     float rE[PX + 1];  // rE[i] = 1 / (z[i+1] - z[i])
     Mask ok[PX + 2];   // sample valid
     Mask hok[PX];      // columns k-1..k+1 valid
+    Mask kE[PX + 1];   // kPairMean: pair rE[i] gives its two pixels a candidate
     // lenient rule with a 3-row filter only: the row's horizontal gradient
     // line at columns 1..PX and whether it has one (computed once, used by
     // the three output rows whose window holds this row)
@@ -331,16 +332,17 @@ template <int KIND, int PX> __device__ __forceinline__ void make_hdiff(Row<PX> &
 
 // A row's values and validity, and for the 3-row filters its horizontal
 // differences (FD needs only those of the middle row: make_middle).
-template <int KIND, int PX, bool HALF, bool FD>
+template <int KIND, int PX, bool HALF, bool FD, bool LEN>
 __device__ __forceinline__ void finish_row(const RawRow<KIND, PX> &raw, Row<PX> &o,
                                            const Edges &e) {
     // lanes that take their outer neighbour from the halo sample
     constexpr Mask kLeft = HALF ? 0x100000001ull : 1ull, kRight = kLeft << (HALF ? 31 : 63);
-    const float h = Raw<KIND>::window(raw.h);
+    // the lenient mean multiplies invalid neighbours by 0: they must be finite
+    const float h = LEN ? Raw<KIND>::value(raw.h) : Raw<KIND>::window(raw.h);
     const Mask okh = mask_of(Raw<KIND>::ok(raw.h));
 #pragma unroll
     for (int k = 0; k < PX; ++k) {
-        o.z[k + 1] = Raw<KIND>::window(raw.x.v[k]);
+        o.z[k + 1] = LEN ? Raw<KIND>::value(raw.x.v[k]) : Raw<KIND>::window(raw.x.v[k]);
         o.ok[k + 1] = mask_of(Raw<KIND>::ok(raw.x.v[k]));
     }
     o.z[0] = left_of<HALF>(h, o.z[PX], e);
@@ -356,11 +358,37 @@ __device__ __forceinline__ void finish_row(const RawRow<KIND, PX> &raw, Row<PX> 
     if constexpr (!FD) make_hdiff<KIND, PX>(o);
 }
 
+// Means over pairs that count their candidates where they are formed: a pair
+// that gives its pixels no candidate (equal values, or under the lenient rule
+// an invalid one) gets the reciprocal 0, once for both pixels, and a mask
+// from which its pixels count what they keep.  For data where such pairs are
+// in nearly every wavefront; the other kinds blank slots in a rare branch.
+// 1024 uneven u16 frames, FD-mean: 1.84 ms (4.05 TB/s of algorithmic bytes),
+// against 1.91 ms with a test, a select and a count in every slot.
+template <int KIND, int AGG, bool LEN>
+constexpr bool kPairMean = AGG == AGG_MEAN && (kTieHeavy<KIND> || LEN);
+
+// 1 / (b - a), or 0 with the bit of `keep` clear if the pair is left out.
+template <bool LEN>
+__device__ __forceinline__ float pair_or_zero(float a, float b, Mask oka, Mask okb, Mask &keep) {
+    keep = mask_of(a != b);
+    if constexpr (LEN) keep &= oka & okb;
+    const float r = rcp(b - a);
+    const bool k = lane(keep);
+    return k ? r : 0.f;
+}
+
 // What only the middle row of the window needs, formed when a row becomes
 // that (earlier it would hold registers): the horizontal pairs.
-template <int KIND, int PX, bool FD> __device__ __forceinline__ void make_middle(Row<PX> &o) {
+template <int KIND, int AGG, int PX, bool FD, bool LEN>
+__device__ __forceinline__ void make_middle(Row<PX> &o) {
 #pragma unroll
-    for (int i = 0; i <= PX; ++i) o.rE[i] = rcp(o.z[i + 1] - o.z[i]);
+    for (int i = 0; i <= PX; ++i) {
+        if constexpr (kPairMean<KIND, AGG, LEN>)
+            o.rE[i] = pair_or_zero<LEN>(o.z[i], o.z[i + 1], o.ok[i], o.ok[i + 1], o.kE[i]);
+        else
+            o.rE[i] = rcp(o.z[i + 1] - o.z[i]);
+    }
     if constexpr (FD) make_hdiff<KIND, PX>(o);
 }
 
@@ -370,16 +398,36 @@ template <int PX> struct Pairs {
     float rS[PX];       // (up k)   - (low k)
     float rSE[PX + 1];  // rSE[i]: (up col i-1) - (low col i)
     float rSW[PX + 1];  // rSW[i]: (up col i)   - (low col i-1)
+    // kPairMean: which of them give candidates, and how many of the three
+    // above a pixel of the lower row do
+    Mask kS[PX], kSE[PX + 1], kSW[PX + 1];
+    int top[PX];
 };
 
-template <int PX>
+template <int KIND, int AGG, bool LEN, int PX>
 __device__ __forceinline__ void make_pairs(const Row<PX> &up, const Row<PX> &lo, Pairs<PX> &o) {
+    if constexpr (kPairMean<KIND, AGG, LEN>) {
 #pragma unroll
-    for (int k = 0; k < PX; ++k) o.rS[k] = rcp(lo.z[k + 1] - up.z[k + 1]);
+        for (int k = 0; k < PX; ++k)
+            o.rS[k] = pair_or_zero<LEN>(up.z[k + 1], lo.z[k + 1], up.ok[k + 1], lo.ok[k + 1],
+                                        o.kS[k]);
 #pragma unroll
-    for (int i = 0; i <= PX; ++i) {
-        o.rSE[i] = rcp(lo.z[i + 1] - up.z[i]);
-        o.rSW[i] = rcp(lo.z[i] - up.z[i + 1]);
+        for (int i = 0; i <= PX; ++i) {
+            o.rSE[i] = pair_or_zero<LEN>(up.z[i], lo.z[i + 1], up.ok[i], lo.ok[i + 1], o.kSE[i]);
+            o.rSW[i] = pair_or_zero<LEN>(up.z[i + 1], lo.z[i], up.ok[i + 1], lo.ok[i], o.kSW[i]);
+        }
+#pragma unroll
+        for (int k = 0; k < PX; ++k)
+            o.top[k] = (lane(o.kS[k]) ? 1 : 0) + (lane(o.kSE[k]) ? 1 : 0) +
+                       (lane(o.kSW[k + 1]) ? 1 : 0);
+    } else {
+#pragma unroll
+        for (int k = 0; k < PX; ++k) o.rS[k] = rcp(lo.z[k + 1] - up.z[k + 1]);
+#pragma unroll
+        for (int i = 0; i <= PX; ++i) {
+            o.rSE[i] = rcp(lo.z[i + 1] - up.z[i]);
+            o.rSW[i] = rcp(lo.z[i] - up.z[i + 1]);
+        }
     }
 }
 
@@ -439,15 +487,18 @@ template <int PX> struct RowState {
     Pairs<PX> below;
 };
 
-// B + the median: 0.5 (x3 + x4), x3 alone if an odd number of values is kept
-// (halving is exact, so the fused form rounds once like B + median).
-__device__ __forceinline__ float median_pair(const float (&t)[8], bool odd, float B) {
+// B + half times the median's double: x3 + x4, or 2 x3 if an odd number
+// of values is kept.
+__device__ __forceinline__ float median_pair(const float (&t)[8], bool odd, float half, float B) {
     float x3, x4;
     middle_pair(t, x3, x4);
-    return fmaf(0.5f, x3 + (odd ? x3 : x4), B);
+    return fmaf(half, x3 + (odd ? x3 : x4), B);
 }
 
-// Candidates t_j = N_j w_j of the 8 slots (see the file header).  Called
+// Candidates t_j = N_j w_j of the 8 slots (see the file header).  For
+// disparity, t_j without its factor -d, which all slots share (a negative
+// factor reverses the order, but the middle one or two stay the same).
+// Called
 // inside each branch of the aggregation so that the min/max network sees
 // values produced in its own basic block (the compiler then knows they are
 // canonical and inserts no quieting instructions).
@@ -457,7 +508,7 @@ __device__ __forceinline__ void candidates(const float (&Nj)[8], const float (&r
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         if constexpr (KIND == KIND_DISP)
-            t[j] = -(Nj[j] * zc) * rj[j];
+            t[j] = Nj[j] * rj[j];
         else
             t[j] = fmaf(Nj[j] * zc, rj[j], Nj[j]);
     }
@@ -480,7 +531,8 @@ __device__ __forceinline__ float median8(const float (&Nj)[8], const float (&rj)
                                          const float (&zj)[8], const Mask (&okj)[8], float zc, float B, bool general) {
     float t[8];
     candidates<KIND>(Nj, rj, zc, t);
-    if (!general) return median_pair(t, false, B);
+    const float half = KIND == KIND_DISP ? -0.5f * zc : 0.5f;
+    if (!general) return median_pair(t, false, half, B);
     float pad = kInf;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -488,32 +540,50 @@ __device__ __forceinline__ float median8(const float (&Nj)[8], const float (&rj)
         t[j] = drop ? pad : t[j];
         pad = drop ? -pad : pad;
     }
-    return median_pair(t, pad < 0.f, B);  // odd number left out -> position 3
+    return median_pair(t, pad < 0.f, half, B);  // odd number left out -> position 3
 }
 
-// B + the mean of the kept candidates.  Both paths add in the same tree
-// order, 1/8 is exact and v_rcp_f32 returns it exactly for m = 8, so a pixel
-// with nothing left out gets the same bits whichever path its wavefront
-// takes.  With nothing kept the sum is +0 and 0 * (1/0) is NaN, which the
-// caller's norm test turns into the degenerate normal.
-template <int KIND, bool LEN>
-__device__ __forceinline__ float mean8(const float (&Nj)[8], const float (&rj)[8],
-                                       const float (&zj)[8], const Mask (&okj)[8], float zc, float B, bool general) {
-    float t[8];
-    candidates<KIND>(Nj, rj, zc, t);
-    float w = 0.125f;
-    if (general) {
-        int m = 0;
+// Sum of the candidates of the 8 slots.  Opposite slots share their N_j up to
+// the sign.  Depth: t_j = N_j z_j rho_j (z_j rho_j = 1 + z rho_j), so a slot
+// whose reciprocal is 0 adds 0.  Disparity: without the factor -d.
+template <int KIND>
+__device__ __forceinline__ float slot_sum(float Gu, float Gv, const float (&rj)[8],
+                                          const float (&zj)[8]) {
+    float q[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const bool drop = left_out<LEN>(zj[j], zc, okj[j]);
-            t[j] = drop ? 0.f : t[j];
-            m += drop ? 0 : 1;
-        }
-        w = rcp((float)m);
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (KIND == KIND_DISP)
+            q[i] = rj[2 * i] - rj[2 * i + 1];
+        else
+            q[i] = fmaf(zj[2 * i], rj[2 * i], -(zj[2 * i + 1] * rj[2 * i + 1]));
     }
-    const float s = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-    return fmaf(s, w, B);
+    return fmaf(Gu, q[0], Gv * q[1]) + fmaf(Gu + Gv, q[2], -((Gu - Gv) * q[3]));
+}
+
+// B + the mean of the kept candidates.  1/8 is exact and v_rcp_f32 returns it
+// exactly for m = 8, so a pixel with nothing left out gets the same bits
+// whichever path its wavefront takes.  With nothing kept the sum is 0 and
+// 0 * (1/0) is NaN, which the caller's norm test turns into the degenerate
+// normal.
+template <int KIND>
+__device__ __forceinline__ float finish_mean(float sum, float weight, float zc, float B) {
+    if constexpr (KIND == KIND_DISP) return fmaf(-(sum * zc), weight, B);
+    return fmaf(sum, weight, B);
+}
+template <int KIND, bool LEN>
+__device__ __forceinline__ float mean8(float Gu, float Gv, const float (&rj)[8],
+                                       const float (&zj)[8], const Mask (&okj)[8], float zc,
+                                       float B, bool general) {
+    if (!general) return finish_mean<KIND>(slot_sum<KIND>(Gu, Gv, rj, zj), 0.125f, zc, B);
+    float r[8];
+    int m = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const bool drop = left_out<LEN>(zj[j], zc, okj[j]);
+        r[j] = drop ? 0.f : rj[j];
+        m += drop ? 0 : 1;
+    }
+    return finish_mean<KIND>(slot_sum<KIND>(Gu, Gv, r, zj), rcp((float)m), zc, B);
 }
 
 // Outputs are written once and not read back by this kernel: nontemporal
@@ -604,17 +674,28 @@ __device__ __forceinline__ float normal_z(int k, const FrameDesc &f, int col, fl
     const float zc = rc.z[c];
     const float fu = (float)(col + k) - f.u0;
     const float B = fmaf(fu, Gu, fv * Gv);
-    const float Spp = Gu + Gv, Spm = Gu - Gv;
     // slots: E, W, S, N, SE, NW, SW, NE
     const float zj[8] = {rc.z[c + 1], rc.z[c - 1], rn.z[c], rp.z[c],
                          rn.z[c + 1], rp.z[c - 1], rn.z[c - 1], rp.z[c + 1]};
-    const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};
     const float rj[8] = {rc.rE[c], -rc.rE[c - 1], pd.rS[k], -pu.rS[k],
                          pd.rSE[c], -pu.rSE[k], pd.rSW[k], -pu.rSW[c]};
     const Mask okj[8] = {rc.ok[c + 1], rc.ok[c - 1], rn.ok[c],     rp.ok[c],
                          rn.ok[c + 1], rp.ok[c - 1], rn.ok[c - 1], rp.ok[c + 1]};
-    return (AGG == AGG_MEAN) ? mean8<KIND, LEN>(Nj, rj, zj, okj, zc, B, GENERAL)
-                             : median8<KIND, LEN>(Nj, rj, zj, okj, zc, B, GENERAL);
+    if constexpr (kPairMean<KIND, AGG, LEN>) {
+        int m = pu.top[k];
+        m += lane(rc.kE[c]) ? 1 : 0;
+        m += lane(rc.kE[c - 1]) ? 1 : 0;
+        m += lane(pd.kS[k]) ? 1 : 0;
+        m += lane(pd.kSE[c]) ? 1 : 0;
+        m += lane(pd.kSW[k]) ? 1 : 0;
+        return finish_mean<KIND>(slot_sum<KIND>(Gu, Gv, rj, zj), rcp((float)m), zc, B);
+    } else if constexpr (AGG == AGG_MEAN) {
+        return mean8<KIND, LEN>(Gu, Gv, rj, zj, okj, zc, B, GENERAL);
+    } else {
+        const float Spp = Gu + Gv, Spm = Gu - Gv;
+        const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};
+        return median8<KIND, LEN>(Nj, rj, zj, okj, zc, B, GENERAL);
+    }
 }
 
 // Output row r of a tile from the window (prev, cur, next); `pend` holds the
@@ -628,7 +709,7 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
                                          RowState<PX> &next) {
     constexpr bool FD = GK == GK_FD;
     constexpr bool LENR = LEN && GK != GK_CUSTOM;  // the lenient rule applies
-    finish_row<KIND, PX, HALF, FD>(pend, next.row, e);
+    finish_row<KIND, PX, HALF, FD, LEN>(pend, next.row, e);
     if constexpr (LENR && !FD) lenient_hlines<KIND, PX>(next.row);
     load_raw<KIND, PX>(ib, r + 1 + SNE_PREFETCH_ROWS, col_off, halo_off, pend);  // prefetch
     // packed output: this row's RGBX bytes, in flight while the row is
@@ -638,8 +719,8 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
         rgbx = buf_load<float, PX>(
             rgbb, (int)((unsigned)r * (unsigned)rgbb.pitch_bytes + (unsigned)(col_off < kOOB
                                                                              ? col * 4 : kOOB)));
-    make_middle<KIND, PX, FD>(cur.row);
-    make_pairs<PX>(cur.row, next.row, cur.below);
+    make_middle<KIND, AGG, PX, FD, LEN>(cur.row);
+    make_pairs<KIND, AGG, LEN, PX>(cur.row, next.row, cur.below);
     const Row<PX> &rp = prev.row, &rc = cur.row, &rn = next.row;
     const Pairs<PX> &pu = prev.below, &pd = cur.below;
 
@@ -679,7 +760,7 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
     // pixels that take the general aggregation whatever the vote below says
     bool general[PX];
 #pragma unroll
-    for (int k = 0; k < PX; ++k) general[k] = kTieHeavy<KIND>;
+    for (int k = 0; k < PX; ++k) general[k] = kTieHeavy<KIND> || kPairMean<KIND, AGG, LEN>;
 
     float Gu[PX], Gv[PX];
     Mask valid[PX];
@@ -748,7 +829,7 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
         // this wavefront needs it (the choice is wave-uniform, and both paths
         // give the same result when nothing is left out).
         // (signs do not matter here: the raw pair values are used)
-        if constexpr (!kTieHeavy<KIND>) {
+        if constexpr (!kTieHeavy<KIND> && !kPairMean<KIND, AGG, LEN>) {
             const int c = k + 1;
             const float rmax = vmax8abs(rc.rE[c], rc.rE[c - 1], pd.rS[k], pu.rS[k], pd.rSE[c],
                                         pu.rSE[k], pd.rSW[k], pu.rSW[c]);
@@ -870,14 +951,14 @@ __device__ __forceinline__ void run_tile(const FrameDesc &f, int c0, int r0, int
     RawRow<KIND, PX> p0;
     RowState<PX> A, B, C;
     load_raw<KIND, PX>(ib, rb - 1, col_off, halo_off, p0);
-    finish_row<KIND, PX, HALF, GK == GK_FD>(p0, A.row, e);
+    finish_row<KIND, PX, HALF, GK == GK_FD, LEN>(p0, A.row, e);
     load_raw<KIND, PX>(ib, rb, col_off, halo_off, p0);
-    finish_row<KIND, PX, HALF, GK == GK_FD>(p0, B.row, e);
+    finish_row<KIND, PX, HALF, GK == GK_FD, LEN>(p0, B.row, e);
     if constexpr (LEN && GK == GK_3ROW) {  // the lenient rule's shared horizontal lines
         lenient_hlines<KIND, PX>(A.row);
         lenient_hlines<KIND, PX>(B.row);
     }
-    make_pairs<PX>(A.row, B.row, A.below);
+    make_pairs<KIND, AGG, LEN, PX>(A.row, B.row, A.below);
     load_raw<KIND, PX>(ib, rb + 1, col_off, halo_off, p0);
 #define SNE_ROW(I, P, X, Y, Z)                                                                  \
     tile_row<KIND, GK, AGG, OUT, PX, HALF, LEN>(f, ib, rgbb, rb + (I), rend, col, col_off, halo_off, \
@@ -1108,7 +1189,7 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
             general = __builtin_amdgcn_ballot_w64(valid && !(rmax < kInf)) != 0;
         }
         const Mask okj[8] = {};  // strict rule: not looked at
-        const float nz = (AGG == AGG_MEAN) ? mean8<KIND, false>(Nj, rj, zj, okj, z0, B, general)
+        const float nz = (AGG == AGG_MEAN) ? mean8<KIND, false>(Gu, Gv, rj, zj, okj, z0, B, general)
                                            : median8<KIND, false>(Nj, rj, zj, okj, z0, B, general);
         const float nx = f.fx * Gu, ny = f.fy * Gv;
         const float n2 = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
