@@ -364,7 +364,9 @@ __device__ __forceinline__ void finish_row(const RawRow<KIND, PX> &raw, Row<PX> 
 // from which its pixels count what they keep.  For data where such pairs are
 // in nearly every wavefront; the other kinds blank slots in a rare branch.
 // 1024 uneven u16 frames, FD-mean: 1.84 ms (4.05 TB/s of algorithmic bytes),
-// against 1.91 ms with a test, a select and a count in every slot.
+// against 1.91 ms with a test, a select and a count in every slot; with the
+// batch kernel's scalar table loads, global stores (store_stream) and the
+// scaled normal (normal_z) 1.75 ms, 4.27 TB/s.
 template <int KIND, int AGG, bool LEN>
 constexpr bool kPairMean = AGG == AGG_MEAN && (kTieHeavy<KIND> || LEN);
 
@@ -549,15 +551,18 @@ __device__ __forceinline__ float median8(const float (&Nj)[8], const float (&rj)
 template <int KIND>
 __device__ __forceinline__ float slot_sum(float Gu, float Gv, const float (&rj)[8],
                                           const float (&zj)[8]) {
-    float q[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if constexpr (KIND == KIND_DISP)
-            q[i] = rj[2 * i] - rj[2 * i + 1];
-        else
-            q[i] = fmaf(zj[2 * i], rj[2 * i], -(zj[2 * i + 1] * rj[2 * i + 1]));
+    // diagonals: N = +-(G_u + G_v) and +-(G_u - G_v), so their terms enter the
+    // sums that multiply G_u and G_v as q2 - q3 and q2 + q3
+    if constexpr (KIND == KIND_DISP) {
+        const float q2 = rj[4] - rj[5], q3 = rj[6] - rj[7];
+        return fmaf(Gu, (rj[0] - rj[1]) + (q2 - q3), Gv * ((rj[2] - rj[3]) + (q2 + q3)));
+    } else {
+        const float q2 = fmaf(zj[4], rj[4], -(zj[5] * rj[5]));
+        const float q3 = fmaf(zj[6], rj[6], -(zj[7] * rj[7]));
+        const float x = fmaf(-zj[1], rj[1], fmaf(zj[0], rj[0], q2 - q3));
+        const float y = fmaf(-zj[3], rj[3], fmaf(zj[2], rj[2], q2 + q3));
+        return fmaf(Gu, x, Gv * y);
     }
-    return fmaf(Gu, q[0], Gv * q[1]) + fmaf(Gu + Gv, q[2], -((Gu - Gv) * q[3]));
 }
 
 // B + the mean of the kept candidates.  1/8 is exact and v_rcp_f32 returns it
@@ -588,24 +593,32 @@ __device__ __forceinline__ float mean8(float Gu, float Gv, const float (&rj)[8],
 
 // Outputs are written once and not read back by this kernel: nontemporal
 // stores keep them from displacing the input rows that neighbouring tiles
-// still read from the caches.
-template <typename V> __device__ __forceinline__ void store_stream(void *p, const V &v) {
+// still read from the caches.  The pointers are cast to the global address
+// space: the uneven batch reads its frames' addresses from memory, and stores
+// through a generic pointer would be flat ones, with a 64-bit address formed
+// per lane instead of a scalar base and a 32-bit offset.
+#define SNE_GLOBAL __attribute__((address_space(1)))
+template <typename V> __device__ __forceinline__ void store_stream(SNE_GLOBAL char *p, const V &v) {
     if constexpr (sizeof(V) == 16) {
         typedef unsigned U __attribute__((ext_vector_type(4)));
-        __builtin_nontemporal_store(__builtin_bit_cast(U, v), static_cast<U *>(p));
+        __builtin_nontemporal_store(__builtin_bit_cast(U, v), (SNE_GLOBAL U *)p);
     } else if constexpr (sizeof(V) == 8) {
         typedef unsigned U __attribute__((ext_vector_type(2)));
-        __builtin_nontemporal_store(__builtin_bit_cast(U, v), static_cast<U *>(p));
+        __builtin_nontemporal_store(__builtin_bit_cast(U, v), (SNE_GLOBAL U *)p);
     } else if constexpr (sizeof(V) == 4) {
-        __builtin_nontemporal_store(__builtin_bit_cast(unsigned, v), static_cast<unsigned *>(p));
+        __builtin_nontemporal_store(__builtin_bit_cast(unsigned, v), (SNE_GLOBAL unsigned *)p);
     } else if constexpr (sizeof(V) == 2) {
         __builtin_nontemporal_store(__builtin_bit_cast(unsigned short, v),
-                                    static_cast<unsigned short *>(p));
+                                    (SNE_GLOBAL unsigned short *)p);
     } else {
         static_assert(sizeof(V) == 1, "store width");
         __builtin_nontemporal_store(__builtin_bit_cast(unsigned char, v),
-                                    static_cast<unsigned char *>(p));
+                                    (SNE_GLOBAL unsigned char *)p);
     }
+}
+// A wave-uniform pointer as a base for store_stream.
+__device__ __forceinline__ SNE_GLOBAL char *store_base(const void *p) {
+    return (SNE_GLOBAL char *)const_cast<void *>(p);
 }
 
 // s_b - s_a of two samples (a before b along the line): for depth
@@ -664,10 +677,12 @@ __device__ __forceinline__ float lenient_combine(float c, Mask hc, float a, Mask
     return g * (centre ? with : without);
 }
 
-// n_z of column k of the middle row: B + Phi over the 8 slots.
+// n_z of column k of the middle row: B + Phi over the 8 slots.  `scale` is a
+// factor that n_x and n_y still need (1 unless set).
 template <int KIND, int AGG, bool LEN, bool GENERAL, int PX>
 __device__ __forceinline__ float normal_z(int k, const FrameDesc &f, int col, float fv, float Gu,
-                                          float Gv, const Row<PX> &rp, const Row<PX> &rc,
+                                          float Gv, float &scale, const Row<PX> &rp,
+                                          const Row<PX> &rc,
                                           const Row<PX> &rn, const Pairs<PX> &pu,
                                           const Pairs<PX> &pd) {
     const int c = k + 1;
@@ -688,7 +703,15 @@ __device__ __forceinline__ float normal_z(int k, const FrameDesc &f, int col, fl
         m += lane(pd.kS[k]) ? 1 : 0;
         m += lane(pd.kSE[c]) ? 1 : 0;
         m += lane(pd.kSW[k]) ? 1 : 0;
-        return finish_mean<KIND>(slot_sum<KIND>(Gu, Gv, rj, zj), rcp((float)m), zc, B);
+        const float sum = slot_sum<KIND>(Gu, Gv, rj, zj);
+        if constexpr (kTieHeavy<KIND>) {
+            // the vector times m instead of the sum divided by it (quantised
+            // depth keeps it far from the ends of the FP32 range); m = 0
+            // gives the zero vector, hence the degenerate normal
+            scale = (float)m;
+            return fmaf(scale, B, sum);
+        }
+        return finish_mean<KIND>(sum, rcp((float)m), zc, B);
     } else if constexpr (AGG == AGG_MEAN) {
         return mean8<KIND, LEN>(Gu, Gv, rj, zj, okj, zc, B, GENERAL);
     } else {
@@ -835,12 +858,17 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
                                         pu.rSE[k], pd.rSW[k], pu.rSW[c]);
             general[k] = general[k] || (mask_of(rmax == kInf) & valid[k]) != 0;
         }
+        float scale = 1.f;
         if (general[k])
-            nz[k] = normal_z<KIND, AGG, LEN, true, PX>(k, f, col, fv, Gu[k], Gv[k], rp, rc, rn, pu,
-                                                       pd);
+            nz[k] = normal_z<KIND, AGG, LEN, true, PX>(k, f, col, fv, Gu[k], Gv[k], scale, rp, rc,
+                                                       rn, pu, pd);
         else
-            nz[k] = normal_z<KIND, AGG, LEN, false, PX>(k, f, col, fv, Gu[k], Gv[k], rp, rc, rn,
-                                                        pu, pd);
+            nz[k] = normal_z<KIND, AGG, LEN, false, PX>(k, f, col, fv, Gu[k], Gv[k], scale, rp, rc,
+                                                        rn, pu, pd);
+        if constexpr (kTieHeavy<KIND> && kPairMean<KIND, AGG, LEN>) {
+            Gu[k] *= scale;
+            Gv[k] *= scale;
+        }
     }
 
     using OT = typename Out<OUT>::T;
@@ -877,7 +905,7 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
     if constexpr (OUT == OUT_RGBN) {
         // one 16-byte pixel: R, G, B (bytes / 255), mask, n_x, n_y, n_z, 0
         if (col < f.W && r < rend) {
-            char *o = static_cast<char *>(f.out) +
+            SNE_GLOBAL char *o = store_base(f.out) +
                       ((unsigned)r * (unsigned)f.out_pitch + (unsigned)col) * 16u;
 #pragma unroll
             for (int k = 0; k < PX; ++k) {
@@ -890,7 +918,7 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
                 typedef _Float16 H8 __attribute__((ext_vector_type(8)));
                 const H8 px = {R, G, Bc, M, ox.v[k], oy.v[k], oz.v[k], (_Float16)0.f};
 #if SNE_RGBN_TEMPORAL
-                *reinterpret_cast<H8 *>(o + 16 * k) = px;
+                *(SNE_GLOBAL H8 *)(o + 16 * k) = px;
 #else
                 store_stream(o + 16 * k, px);
 #endif
@@ -899,13 +927,15 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
                 typename MaskWord<PX>::T w = 0;
 #pragma unroll
                 for (int k = 0; k < PX; ++k) w |= (typename MaskWord<PX>::T)mk[k] << (8 * k);
-                store_stream(f.mask + ((unsigned)r * (unsigned)f.mask_pitch + (unsigned)col), w);
+                store_stream(store_base(f.mask) +
+                                 ((unsigned)r * (unsigned)f.mask_pitch + (unsigned)col),
+                             w);
             }
         }
     } else if (col < f.W && r < rend) {
         // uniform plane bases + one 32-bit byte offset per lane (the host
         // keeps each plane below 4 GiB)
-        char *o = static_cast<char *>(f.out);
+        SNE_GLOBAL char *o = store_base(f.out);
         const int64_t plane = f.out_plane * (int64_t)sizeof(OT);
         const unsigned off = ((unsigned)r * (unsigned)f.out_pitch + (unsigned)col) * sizeof(OT);
         store_stream(o + off, ox);
@@ -915,7 +945,9 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
             typename MaskWord<PX>::T w = 0;
 #pragma unroll
             for (int k = 0; k < PX; ++k) w |= (typename MaskWord<PX>::T)mk[k] << (8 * k);
-            store_stream(f.mask + ((unsigned)r * (unsigned)f.mask_pitch + (unsigned)col), w);
+            store_stream(store_base(f.mask) +
+                                 ((unsigned)r * (unsigned)f.mask_pitch + (unsigned)col),
+                             w);
         }
     }
 }
@@ -1200,30 +1232,36 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
         const OT oy = Out<OUT>::cvt(keep ? -ny * inv : 0.f);
         const OT oz = Out<OUT>::cvt(keep ? nz * inv : (valid ? -1.f : 0.f));
         if (x < f.W && y < f.H) {
-            char *o = static_cast<char *>(f.out);
+            SNE_GLOBAL char *o = store_base(f.out);
             const int64_t plane = f.out_plane * (int64_t)sizeof(OT);
-            const int64_t off = ((int64_t)y * f.out_pitch + x) * (int64_t)sizeof(OT);
+            const unsigned off = ((unsigned)y * (unsigned)f.out_pitch + (unsigned)x) * sizeof(OT);
             store_stream(o + off, ox);
             store_stream(o + plane + off, oy);
             store_stream(o + 2 * plane + off, oz);
-            if (f.mask) store_stream(f.mask + (int64_t)y * f.mask_pitch + x, (uint8_t)valid);
+            if (f.mask)
+                store_stream(store_base(f.mask) +
+                                 ((unsigned)y * (unsigned)f.mask_pitch + (unsigned)x),
+                             (uint8_t)valid);
         }
     }
 }
 
-// A value loaded through a generic pointer counts as lane-varying for the
-// compiler, even at a wave-uniform address.  The batch tables are only read
-// at wave-uniform addresses: moving every dword to a scalar register keeps
-// the frame's buffer resource and constants in SGPRs (otherwise each buffer
-// load of the tile becomes a loop over distinct resources).
+// The batch tables are only read at wave-uniform addresses and do not change
+// while the kernel runs (the queue heads apart, which are not read here):
+// loads through the constant address space go to scalar registers directly,
+// which keeps a frame's buffer resource and constants there (loaded through a
+// generic pointer they would count as lane-varying, and each buffer load of
+// the tile would become a loop over distinct resources).
 template <typename T> __device__ __forceinline__ T uniform_load(const T *p) {
     static_assert(sizeof(T) % 4 == 0, "dword-sized table entries");
     struct Words {
         int w[sizeof(T) / 4];
     };
-    Words v = __builtin_bit_cast(Words, *p);
+    typedef const __attribute__((address_space(4))) int CInt;
+    CInt *c = (CInt *)p;
+    Words v;
 #pragma unroll
-    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) v.w[i] = __builtin_amdgcn_readfirstlane(v.w[i]);
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) v.w[i] = c[i];
     return __builtin_bit_cast(T, v);
 }
 
@@ -1238,7 +1276,7 @@ __device__ __forceinline__ int find_frame(const int32_t *tile_start, int nframes
     while (lo < hi) {
         const int step = (hi - lo + kWave) / kWave;  // ceil((hi - lo + 1) / 64)
         const int probe = lo + lane * step;
-        const int32_t v = tile_start[min(probe, hi)];  // in bounds for every lane
+        const int32_t v = ((SNE_GLOBAL const int32_t *)tile_start)[min(probe, hi)];  // in bounds
         const bool le = probe <= hi && v <= tile;
         const uint64_t m = __builtin_amdgcn_ballot_w64(le);  // lanes 0..k, k >= 0
         const int k = 63 - __builtin_clzll(m);
@@ -1271,12 +1309,14 @@ __global__ __launch_bounds__(kBlock) SNE_BATCH_OCCUPANCY void sne_batch_kernel(B
         // reads instead of queueing eight atomics each on the same lines.
         int seen = 0;
         if (lane == 0)
-            seen = __hip_atomic_load(&head->queue[q].next, __ATOMIC_RELAXED,
+            seen = __hip_atomic_load((SNE_GLOBAL int32_t *)&head->queue[q].next, __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_AGENT);
         if (__builtin_amdgcn_readfirstlane(seen) >= end - begin) continue;
         for (;;) {
             int taken = 0;
-            if (lane == 0) taken = atomicAdd(&head->queue[q].next, a.chunk);
+            if (lane == 0)
+                taken = __hip_atomic_fetch_add((SNE_GLOBAL int32_t *)&head->queue[q].next, a.chunk,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             taken = __builtin_amdgcn_readfirstlane(taken);  // lane 0 is the first active lane
             const int first = begin + min(taken, end - begin);
             if (first >= end) break;
