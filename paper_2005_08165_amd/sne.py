@@ -210,8 +210,16 @@ def _on_gpu(*tensors) -> None:
             raise ValueError("tensors passed to the library must be on the GPU, got %s" % t.device)
 
 
+# The handle of a device's current stream without the torch.cuda.Stream object
+# that torch.cuda.current_stream() builds around it (about 2 us of the 11 us
+# that a single-frame call took on the host).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
@@ -229,16 +237,17 @@ def _sync(stream) -> None:
 
 
 def _K(K: Sequence[float]) -> Intrinsics:
-    fx, fy, u0, v0 = (float(x) for x in K)
-    return Intrinsics(fx, fy, u0, v0)
+    fx, fy, u0, v0 = K
+    return Intrinsics(float(fx), float(fy), float(u0), float(v0))
 
 
 def _enum(table, key, what):
     if isinstance(key, int):
         return key
-    if key not in table:
+    code = table.get(key)
+    if code is None:
         raise ValueError("unknown %s %r" % (what, key))
-    return table[key]
+    return code
 
 
 SNE_LENIENT = 0x100  # include/sne.h
@@ -249,6 +258,9 @@ def _kind(kind) -> int:
     SNE_LENIENT, the rule for holes and the frame border."""
     if isinstance(kind, int):
         return kind
+    code = KIND.get(kind)
+    if code is not None:
+        return code
     base, plus, rule = kind.partition("+")
     code = _enum(KIND, base, "kind")
     if plus:
@@ -507,12 +519,14 @@ class Server:
         """(normals [3,H,W], mask [H,W]) of a completion, copied out of the
         arena (the arena slot is still held until release)."""
         dt = OUT_DTYPE[self.out]
-        esz = torch.tensor([], dtype=dt).element_size()
+        esz = dt.itemsize
         n = torch.empty((3, c.H, c.W), dtype=dt, device="cuda")
         m = torch.empty((c.H, c.W), dtype=torch.uint8, device="cuda")
-        torch.cuda.synchronize()
-        _memcpy_d2d(n.data_ptr(), c.normals, 3 * c.H * c.W * esz)
-        _memcpy_d2d(m.data_ptr(), c.mask, c.H * c.W)
+        # the batch is done (its completion was polled), so the copies need no
+        # wait before them; one wait after both, as the caller may release the
+        # arena's memory next
+        px = c.H * c.W
+        _memcpy_d2d(((n.data_ptr(), c.normals, 3 * px * esz), (m.data_ptr(), c.mask, px)))
         return n, m
 
     def release(self, ticket: int):
@@ -594,15 +608,19 @@ def simulate(stream_shapes: Sequence[Tuple[int, int]], total_rate: float, durati
     return st.as_dict()
 
 
-def _memcpy_d2d(dst: int, src: int, nbytes: int):
-    """Device-to-device copy of nbytes on the current stream (plumbing)."""
+def _memcpy_d2d(copies):
+    """Device-to-device copies (dst, src, nbytes) on the current stream, waited
+    for together (plumbing)."""
     s = torch.cuda.current_stream()
     hip = _hip()
-    rc = hip.hipMemcpyAsync(ctypes.c_void_p(dst), ctypes.c_void_p(src), ctypes.c_size_t(nbytes),
-                            3, ctypes.c_void_p(s.cuda_stream))
-    if rc != 0:
-        raise RuntimeError("hipMemcpyAsync failed (%d)" % rc)
-    s.synchronize()
+    try:
+        for dst, src, nbytes in copies:
+            rc = hip.hipMemcpyAsync(ctypes.c_void_p(dst), ctypes.c_void_p(src),
+                                    ctypes.c_size_t(nbytes), 3, ctypes.c_void_p(s.cuda_stream))
+            if rc != 0:
+                raise RuntimeError("hipMemcpyAsync failed (%d)" % rc)
+    finally:
+        s.synchronize()
 
 
 _hiplib = None
@@ -618,19 +636,30 @@ def _hip():
 
 
 def _outputs(raw, out_i, normals, mask, want_mask):
+    """Checked (or allocated) outputs of a [..., H, W] input, as (normals,
+    mask, raw strides, normal strides, mask strides or None)."""
     _on_gpu(raw, normals, mask)
-    shape = tuple(raw.shape[:-2]) + (3,) + tuple(raw.shape[-2:])
+    size = tuple(raw.shape)
+    shape = size[:-2] + (3,) + size[-2:]
+    dtype = OUT_DTYPE[out_i]
     if normals is None:
-        normals = torch.empty(shape, dtype=OUT_DTYPE[out_i], device=raw.device)
-    if tuple(normals.shape) != shape or normals.dtype != OUT_DTYPE[out_i]:
-        raise ValueError("normals must be %s %s" % (shape, OUT_DTYPE[out_i]))
-    if normals.stride(-3) != raw.shape[-2] * _row_pitch(normals):
+        normals = torch.empty(shape, dtype=dtype, device=raw.device)
+    if tuple(normals.shape) != shape or normals.dtype != dtype:
+        raise ValueError("normals must be %s %s" % (shape, dtype))
+    rs, ns, ms = raw.stride(), normals.stride(), None
+    if ns[-1] != 1 or rs[-1] != 1:
+        raise ValueError("images need a unit column stride")
+    if ns[-3] != size[-2] * ns[-2]:
         raise ValueError("normal channels must be H * row_pitch apart")
     if mask is None and want_mask:
-        mask = torch.empty(tuple(raw.shape), dtype=torch.uint8, device=raw.device)
-    if mask is not None and (tuple(mask.shape) != tuple(raw.shape) or mask.dtype != torch.uint8):
-        raise ValueError("mask must be %s uint8" % (tuple(raw.shape),))
-    return normals, mask
+        mask = torch.empty(size, dtype=torch.uint8, device=raw.device)
+    if mask is not None:
+        if tuple(mask.shape) != size or mask.dtype != torch.uint8:
+            raise ValueError("mask must be %s uint8" % (size,))
+        ms = mask.stride()
+        if ms[-1] != 1:
+            raise ValueError("images need a unit column stride")
+    return normals, mask, rs, ns, ms
 
 
 def estimate(raw: torch.Tensor, K, kind="depth_f32", grad="fd", agg="mean", out="f32",
@@ -641,15 +670,14 @@ def estimate(raw: torch.Tensor, K, kind="depth_f32", grad="fd", agg="mean", out=
         raise ValueError("expected [H, W]")
     if raw.dtype != _dtype(kind_i):
         raise TypeError("kind %s needs %s input" % (kind, _dtype(kind_i)))
-    normals, mask = _outputs(raw, out_i, normals, mask, want_mask)
+    normals, mask, rs, ns, ms = _outputs(raw, out_i, normals, mask, want_mask)
     H, W = raw.shape
-    Kc = _K(K)
-    st = lib().sne_estimate(None if ctx is None else ctx.handle, raw.data_ptr(), H, W,
-                            _row_pitch(raw), ctypes.byref(Kc), kind_i, _enum(GRAD, grad, "grad"),
-                            _enum(AGG, agg, "agg"), out_i, normals.data_ptr(),
-                            _row_pitch(normals), _ptr(mask),
-                            0 if mask is None else _row_pitch(mask), _stream(stream))
-    check("sne_estimate", st)
+    st = (_lib or lib()).sne_estimate(
+        None if ctx is None else ctx._h, raw.data_ptr(), H, W, rs[0], _K(K), kind_i,
+        _enum(GRAD, grad, "grad"), _enum(AGG, agg, "agg"), out_i, normals.data_ptr(), ns[1],
+        None if mask is None else mask.data_ptr(), 0 if mask is None else ms[0], _stream(stream))
+    if st != SNE_OK:
+        check("sne_estimate", st)
     return normals, mask
 
 
@@ -663,16 +691,15 @@ def estimate_uniform(raw: torch.Tensor, K, kind="depth_f32", grad="fd", agg="mea
         raise ValueError("expected [B, H, W]")
     if raw.dtype != _dtype(kind_i):
         raise TypeError("kind %s needs %s input" % (kind, _dtype(kind_i)))
-    normals, mask = _outputs(raw, out_i, normals, mask, want_mask)
+    normals, mask, rs, ns, ms = _outputs(raw, out_i, normals, mask, want_mask)
     B, H, W = raw.shape
-    Kc = _K(K)
-    st = lib().sne_estimate_uniform(
-        None if ctx is None else ctx.handle, raw.data_ptr(), B, H, W, _row_pitch(raw),
-        raw.stride(0), ctypes.byref(Kc), kind_i, _enum(GRAD, grad, "grad"),
-        _enum(AGG, agg, "agg"), out_i, normals.data_ptr(), _row_pitch(normals),
-        normals.stride(0), _ptr(mask), 0 if mask is None else _row_pitch(mask),
-        0 if mask is None else mask.stride(0), _stream(stream))
-    check("sne_estimate_uniform", st)
+    st = (_lib or lib()).sne_estimate_uniform(
+        None if ctx is None else ctx._h, raw.data_ptr(), B, H, W, rs[1], rs[0], _K(K), kind_i,
+        _enum(GRAD, grad, "grad"), _enum(AGG, agg, "agg"), out_i, normals.data_ptr(), ns[2],
+        ns[0], None if mask is None else mask.data_ptr(), 0 if mask is None else ms[1],
+        0 if mask is None else ms[0], _stream(stream))
+    if st != SNE_OK:
+        check("sne_estimate_uniform", st)
     return normals, mask
 
 
