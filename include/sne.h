@@ -247,8 +247,9 @@ typedef struct {
 } sne_tile;
 
 /* Force a tile shape for every later call on ctx (rows = 0 restores the
- * autotuned/default choice).  A shape the frame's alignment cannot use falls
- * back to a narrower cols_per_lane. */
+ * autotuned/default choice).  Rows may start at any address that is a multiple
+ * of the element size; a frame narrower than cols_per_lane falls back to fewer
+ * columns. */
 int sne_set_tile(sne_ctx *ctx, const sne_tile *tile);
 
 /* The tile shape ctx would use for a batch of B dense frames (row pitch W)

@@ -103,44 +103,69 @@ void grad_weights(int grad, GradW &w) {
 
 bool aligned(const void *p, size_t bytes) { return ((uintptr_t)p % bytes) == 0; }
 
-// Widest columns-per-lane the buffers' alignment allows.
-int max_px(const void *in, const void *out, const uint8_t *mask, int W, int64_t in_pitch,
-           int64_t out_pitch, int64_t mask_pitch, int64_t in_fs, int64_t out_fs, int64_t mask_fs,
-           int64_t out_plane, int kind, int out_type) {
-    for (int px : {4, 2}) {
-        bool ok = (W % px == 0) && (in_pitch % px == 0) && (out_pitch % px == 0) &&
-                  (in_fs % px == 0) && (out_fs % px == 0) && (out_plane % px == 0) &&
-                  aligned(in, px * in_elem(kind)) && aligned(out, px * out_elem(out_type));
-        if (mask) ok = ok && (mask_pitch % px == 0) && (mask_fs % px == 0) && aligned(mask, px);
-        if (ok) return px;
-    }
-    return 1;
+// Most columns per lane for a frame.  The kernels' vector loads and stores
+// take any alignment of the elements, and the lane that a width not divisible
+// by the columns cuts is handled (Tail), so rows may start anywhere: only a
+// frame narrower than the vector, or a pointer not aligned to its elements,
+// goes narrower.  Against one column per lane, which odd widths used to get,
+// four take 427 x 561 FP16 frames (9 in a batch) from 12.6 to 11.5 us.
+int max_px(const void *in, const void *out, int W, int kind, int out_type) {
+    if (!aligned(in, in_elem(kind)) || !aligned(out, out_elem(out_type))) return 1;
+    return W >= 4 ? 4 : W >= 2 ? 2 : 1;
 }
 
 int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 
-// Heuristic tile shape when nothing is cached: fewest idle lanes in the last
-// strip (full or half-wave strips), then enough wavefronts to cover every CU
-// several times.
-TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax) {
-    TileChoice best{1, 2, 1, 0};
-    int64_t best_waste = -1;
+// Tile shape when nothing is cached, fitted to sweeps over 20 workloads (one
+// frame to 100, widths 400 to 3840, every input kind; the choice is within
+// 10 % of the best shape of each but for a few small batches).
+//
+// Columns per lane and half waves: the least work per row of the frame.  A
+// lane's row costs about 40 + 60 px instructions whatever its columns hold;
+// half waves cost 5 % more, and 30 % where rows do not start at multiples of
+// their 4-column vectors (20 x 1001x1333 FP32 Scharr-median: 133 us in half
+// waves, 98 in full ones).  The lenient rule's kernels hold so many registers
+// at 4 columns that 2 are faster (64 x 480x640: 87 against 101 us).
+//
+// Rows: 8 where there are enough tiles for it, 4 otherwise (the first row of
+// a tile costs about two); FP32 rows of a width that is no multiple of 256 bytes
+// share a cache line between the wavefronts of neighbouring strips, which
+// should write it at about the same time: 4, or 2 in large batches (40 x
+// 500x1242 disparity Sobel-mean: 2 rows 84-91 us, 4 rows 102, 8 rows 109;
+// with padded rows, Scharr-median, 70, 73 and 84 us).
+// Uneven batches: 20 rows (the persistent kernel finds a frame per tile) if
+// that leaves enough tiles.
+//
+// Blocks go out in runs of kChunkOrder per XCD, which is the best or within
+// 3 % of it everywhere.
+TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, const Variant &v,
+                        bool uneven) {
+    TileChoice best{1, 4, kChunkOrder, 0};
+    double best_cost = 0.0;
+    const int widest = (v.kind & SNE_LENIENT) ? std::min(pxmax, 2) : pxmax;
     for (int px : {4, 2, 1}) {
-        if (px > pxmax) continue;
+        if (px > widest) continue;
         for (int half : {0, 1}) {
-            TileChoice t{px, 2, 1, half};
-            const int64_t span = tile_cols(t);
-            const int64_t waste = ((W + span - 1) / span) * span - W;
-            if (best_waste < 0 || waste < best_waste) {
+            const TileChoice t{px, 4, kChunkOrder, half};
+            const double lanes = (double)tile_nstrips(W, t) * (half ? 32 : 64);
+            const double cost = lanes * (40 + 60 * px) * (!half ? 1.0 : W % 4 ? 1.3 : 1.05);
+            if (best_cost == 0.0 || cost < best_cost) {
                 best = t;
-                best_waste = waste;
+                best_cost = cost;
             }
         }
     }
-    const int64_t nstrips = tile_nstrips(W, best);
-    const int64_t target = (int64_t)(ctx ? ctx->num_cu : 256) * 16;  // wavefronts
-    int64_t rows = (B * H * nstrips) / std::max<int64_t>(target, 1) / (best.half ? 2 : 1);
-    best.rows = (int)std::min<int64_t>(std::max<int64_t>(rows, 2), 32);
+    // tiles of 1 row, in wavefronts; 4 per SIMD are resident
+    const int64_t waves = B * H * tile_nstrips(W, best) / (best.half ? 2 : 1);
+    const int64_t full = (int64_t)(ctx ? ctx->num_cu : 256) * 16;
+    if (uneven) {
+        best.rows = (int)std::min<int64_t>(std::max<int64_t>(waves / full, 2), 20);
+        return best;
+    }
+    best.rows = 8;
+    if (v.out == SNE_OUT_F32 && W * 4 % kRowAlign != 0)
+        best.rows = !(v.kind & SNE_LENIENT) && B * H * W > (16 << 20) ? 2 : 4;
+    if (best.rows == 8 && waves / 8 < full * 9 / 10) best.rows = 4;
     return best;
 }
 
@@ -175,7 +200,7 @@ TileChoice pick_tile(const sne_ctx *ctx, int H, int W, int64_t B, const Variant 
             if (layout == 0) break;
         }
     }
-    return default_tile(ctx, H, W, B, pxmax);
+    return default_tile(ctx, H, W, B, pxmax, v, uneven);
 }
 
 hipError_t launch_uniform(const Variant &v, const UniformArgs &a, int grid, hipStream_t s) {
@@ -273,9 +298,7 @@ int scan_batch(const sne_ctx *ctx, const sne_frame *frames, int32_t n, int kind,
         if (!valid_K_row(ctx, f.k_index, kind)) return SNE_ERR_ARG;
         if (!frame_fits(f.H, f.in_pitch, kind, f.out_pitch, out_type, f.mask ? f.mask_pitch : 0))
             return SNE_ERR_UNSUPPORTED;
-        pxmax = std::min(pxmax, max_px(f.in, f.normals, f.mask, f.W, f.in_pitch, f.out_pitch,
-                                       f.mask_pitch, 0, 0, 0, (int64_t)f.H * f.out_pitch, kind,
-                                       out_type));
+        pxmax = std::min(pxmax, max_px(f.in, f.normals, f.W, kind, out_type));
         maxH = std::max(maxH, (int)f.H);
         maxW = std::max(maxW, (int)f.W);
     }
@@ -355,13 +378,9 @@ int uniform_impl(sne_ctx *ctx, const void *in, int32_t B, int32_t H, int32_t W, 
         if (hipSetDevice(ctx->device) != hipSuccess) return SNE_ERR_HIP;
         return launch_wide(v, w, (hipStream_t)stream) == hipSuccess ? SNE_OK : SNE_ERR_HIP;
     }
-    int pxmax = max_px(in, normals, mask, W, in_pitch, packed ? 8 * out_pitch : out_pitch,
-                       mask_pitch, in_fs, out_fs, mask_fs, packed ? 8 * plane : plane, kind,
-                       packed ? SNE_OUT_F16 : out_type);
-    if (packed && rgb->rgb)  // RGBX vector loads of px pixels
-        while (pxmax > 1 && (rgb->pitch % (4 * pxmax) || rgb_fs % (4 * pxmax) ||
-                             !aligned(rgb->rgb, 4 * pxmax)))
-            pxmax >>= 1;
+    int pxmax = max_px(in, normals, W, kind, packed ? SNE_OUT_F16 : out_type);
+    if (packed)  // the packed branch stores whole lanes only
+        while (W % pxmax) pxmax >>= 1;
     const int64_t orow = packed ? 16 * out_pitch : out_pitch * (int64_t)out_elem(out_type);
     const int layout =
         row_layout(in, in_pitch * (int64_t)in_elem(kind), in_fs * (int64_t)in_elem(kind)) &&
@@ -903,8 +922,7 @@ int sne_autotune_pitched(sne_ctx *ctx, int32_t H, int32_t W, int32_t B, int64_t 
             hipLaunchKernelGGL(fill_pattern<uint16_t>, dim3(blocks), dim3(threads), 0, st,
                                (uint16_t *)in, nfill, (int)in_pitch, base);
         sne_intrinsics K{(float)W, (float)W, (W - 1) * 0.5f, (H - 1) * 0.5f};
-        const int pxmax = max_px(in, out, mask, W, in_pitch, out_pitch, out_pitch, ifr, 3 * ofr,
-                                 ofr, ofr, kind, out_type);
+        const int pxmax = max_px(in, out, W, kind, out_type);
         layout = row_layout(in, in_pitch * (int64_t)in_elem(kind), ifr * in_elem(kind)) &&
                  row_layout(out, out_pitch * (int64_t)out_elem(out_type),
                             ofr * out_elem(out_type));
@@ -917,7 +935,9 @@ int sne_autotune_pitched(sne_ctx *ctx, int32_t H, int32_t W, int32_t B, int64_t 
             return uniform_impl(ctx, src, B, H, W, in_pitch, ifr, &K, kind, grad, agg, out_type,
                                 dst, out_pitch, 3 * ofr, msk, out_pitch, ofr, st, &t) == SNE_OK;
         };
-        best = pick_fastest(tile_candidates(H, pxmax, true), default_tile(ctx, H, W, B, pxmax),
+        const Variant v{kind, grad, agg, out_type, 1};
+        best = pick_fastest(tile_candidates(H, pxmax, true),
+                            default_tile(ctx, H, W, B, pxmax, v, false),
                             launch, st, e0, e1);
         if (best.rows == 0) rc = SNE_ERR_HIP;
     }

@@ -90,9 +90,7 @@ inline bool frame_fits(int64_t H, int64_t in_pitch, int kind, int64_t out_pitch,
 }
 
 void grad_weights(int grad, GradW &w);
-int max_px(const void *in, const void *out, const uint8_t *mask, int W, int64_t in_pitch,
-           int64_t out_pitch, int64_t mask_pitch, int64_t in_fs, int64_t out_fs, int64_t mask_fs,
-           int64_t out_plane, int kind, int out_type);
+int max_px(const void *in, const void *out, int W, int kind, int out_type);
 FrameDesc make_desc(const void *in, void *out, uint8_t *mask, int H, int W, int64_t in_pitch,
                     int64_t out_pitch, int64_t mask_pitch, const sne_intrinsics &K);
 hipError_t launch_batch(const Variant &v, const BatchArgs &a, int grid, hipStream_t s);

@@ -263,6 +263,39 @@ template <> __device__ __forceinline__ Vec<uint16_t, 4> buf_load<uint16_t, 4>(co
     return __builtin_bit_cast(Vec<uint16_t, 4>, __builtin_amdgcn_raw_buffer_load_b64(b.rsrc, off, 0, 0));
 }
 
+// The lane that holds a row's last columns when the width is not a multiple
+// of PX.  It loads the row's last PX samples (all inside the frame) and moves
+// the ones it owns to the front; the columns past the width become 0, which
+// is invalid.  `any` is wave-uniform: tiles without such a lane pass by.
+struct Tail {
+    bool any;  // a lane of this tile is cut
+    int skip;  // samples this lane drops from the front (0 for whole lanes)
+};
+template <int PX>
+__device__ __forceinline__ void shift_down(Vec<float, PX> &x, int skip) {
+    if constexpr (PX == 4) {
+        const bool two = (skip & 2) != 0;
+        x.v[0] = two ? x.v[2] : x.v[0];
+        x.v[1] = two ? x.v[3] : x.v[1];
+        x.v[2] = two ? 0.f : x.v[2];
+        x.v[3] = two ? 0.f : x.v[3];
+    }
+    if constexpr (PX >= 2) {
+        const bool one = (skip & 1) != 0;
+#pragma unroll
+        for (int k = 0; k < PX; ++k) x.v[k] = one ? (k + 1 < PX ? x.v[k + 1] : 0.f) : x.v[k];
+    }
+}
+template <int PX>
+__device__ __forceinline__ void shift_down(Vec<uint16_t, PX> &x, int skip) {
+    if constexpr (PX == 4)
+        x = __builtin_bit_cast(Vec<uint16_t, PX>,
+                               __builtin_bit_cast(uint64_t, x) >> (16 * skip));
+    if constexpr (PX == 2)
+        x = __builtin_bit_cast(Vec<uint16_t, PX>,
+                               __builtin_bit_cast(uint32_t, x) >> (16 * skip));
+}
+
 // Issue the loads of row r; everything outside the frame reads as 0.
 // col_off / halo_off: this lane's byte offsets within a row, kOOB-based when
 // the lane loads nothing.
@@ -333,8 +366,10 @@ template <int KIND, int PX> __device__ __forceinline__ void make_hdiff(Row<PX> &
 // A row's values and validity, and for the 3-row filters its horizontal
 // differences (FD needs only those of the middle row: make_middle).
 template <int KIND, int PX, bool HALF, bool FD, bool LEN>
-__device__ __forceinline__ void finish_row(const RawRow<KIND, PX> &raw, Row<PX> &o,
-                                           const Edges &e) {
+__device__ __forceinline__ void finish_row(RawRow<KIND, PX> &raw, Row<PX> &o,
+                                           const Edges &e, const Tail &tail) {
+    if constexpr (PX > 1)
+        if (tail.any) shift_down<PX>(raw.x, tail.skip);
     // lanes that take their outer neighbour from the halo sample
     constexpr Mask kLeft = HALF ? 0x100000001ull : 1ull, kRight = kLeft << (HALF ? 31 : 63);
     // the lenient mean multiplies invalid neighbours by 0: they must be finite
@@ -597,23 +632,47 @@ __device__ __forceinline__ float mean8(float Gu, float Gv, const float (&rj)[8],
 // space: the uneven batch reads its frames' addresses from memory, and stores
 // through a generic pointer would be flat ones, with a 64-bit address formed
 // per lane instead of a scalar base and a 32-bit offset.
+// The vectors are only as aligned as their elements (rows of any width start
+// anywhere): the GPU's memory instructions take any alignment.
 #define SNE_GLOBAL __attribute__((address_space(1)))
 template <typename V> __device__ __forceinline__ void store_stream(SNE_GLOBAL char *p, const V &v) {
     if constexpr (sizeof(V) == 16) {
-        typedef unsigned U __attribute__((ext_vector_type(4)));
+        typedef unsigned U __attribute__((ext_vector_type(4), aligned(1)));
         __builtin_nontemporal_store(__builtin_bit_cast(U, v), (SNE_GLOBAL U *)p);
     } else if constexpr (sizeof(V) == 8) {
-        typedef unsigned U __attribute__((ext_vector_type(2)));
+        typedef unsigned U __attribute__((ext_vector_type(2), aligned(1)));
         __builtin_nontemporal_store(__builtin_bit_cast(U, v), (SNE_GLOBAL U *)p);
     } else if constexpr (sizeof(V) == 4) {
-        __builtin_nontemporal_store(__builtin_bit_cast(unsigned, v), (SNE_GLOBAL unsigned *)p);
+        typedef unsigned U __attribute__((aligned(1)));
+        __builtin_nontemporal_store(__builtin_bit_cast(U, v), (SNE_GLOBAL U *)p);
     } else if constexpr (sizeof(V) == 2) {
-        __builtin_nontemporal_store(__builtin_bit_cast(unsigned short, v),
-                                    (SNE_GLOBAL unsigned short *)p);
+        typedef unsigned short U __attribute__((aligned(1)));
+        __builtin_nontemporal_store(__builtin_bit_cast(U, v), (SNE_GLOBAL U *)p);
     } else {
         static_assert(sizeof(V) == 1, "store width");
         __builtin_nontemporal_store(__builtin_bit_cast(unsigned char, v),
                                     (SNE_GLOBAL unsigned char *)p);
+    }
+}
+// The first sizeof(V) / sizeof(E) - skip elements of a vector, one by one
+// (Tail).  The vector is taken as it was packed for the whole lanes: asking
+// for its elements would make the compiler convert them one by one for those
+// too.
+template <typename E, typename V>
+__device__ __forceinline__ void store_front(SNE_GLOBAL char *p, const V &v, int skip) {
+    constexpr int N = (int)(sizeof(V) / sizeof(E));
+    constexpr int W = (int)((sizeof(V) + 3) / 4), kPer = (int)(4 / sizeof(E));
+    uint32_t w[W] = {};
+    __builtin_memcpy(w, &v, sizeof(V));
+#pragma unroll
+    for (int i = 0; i < W; ++i) asm("" : "+v"(w[i]));
+#pragma unroll
+    for (int k = 0; k + 1 < N; ++k) {
+        if (k + skip >= N) break;
+        const uint32_t bits = w[k / kPer] >> (8 * sizeof(E) * (k % kPer));
+        if constexpr (sizeof(E) == 4) store_stream(p + 4 * k, bits);
+        else if constexpr (sizeof(E) == 2) store_stream(p + 2 * k, (uint16_t)bits);
+        else store_stream(p + k, (uint8_t)bits);
     }
 }
 // A wave-uniform pointer as a base for store_stream.
@@ -727,12 +786,13 @@ __device__ __forceinline__ float normal_z(int k, const FrameDesc &f, int col, fl
 template <int KIND, int GK, int AGG, int OUT, int PX, bool HALF, bool LEN>
 __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, const InBuf &rgbb,
                                          int r, int rend, int col, int col_off, int halo_off,
-                                         const Edges &e, const GradW &gw, RawRow<KIND, PX> &pend,
+                                         const Edges &e, const Tail &tail, const GradW &gw,
+                                         RawRow<KIND, PX> &pend,
                                          const RowState<PX> &prev, RowState<PX> &cur,
                                          RowState<PX> &next) {
     constexpr bool FD = GK == GK_FD;
     constexpr bool LENR = LEN && GK != GK_CUSTOM;  // the lenient rule applies
-    finish_row<KIND, PX, HALF, FD, LEN>(pend, next.row, e);
+    finish_row<KIND, PX, HALF, FD, LEN>(pend, next.row, e, tail);
     if constexpr (LENR && !FD) lenient_hlines<KIND, PX>(next.row);
     load_raw<KIND, PX>(ib, r + 1 + SNE_PREFETCH_ROWS, col_off, halo_off, pend);  // prefetch
     // packed output: this row's RGBX bytes, in flight while the row is
@@ -932,23 +992,31 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
                              w);
             }
         }
-    } else if (col < f.W && r < rend) {
+    } else {
         // uniform plane bases + one 32-bit byte offset per lane (the host
         // keeps each plane below 4 GiB)
         SNE_GLOBAL char *o = store_base(f.out);
         const int64_t plane = f.out_plane * (int64_t)sizeof(OT);
         const unsigned off = ((unsigned)r * (unsigned)f.out_pitch + (unsigned)col) * sizeof(OT);
-        store_stream(o + off, ox);
-        store_stream(o + plane + off, oy);
-        store_stream(o + 2 * plane + off, oz);
+        const unsigned moff = (unsigned)r * (unsigned)f.mask_pitch + (unsigned)col;
+        typename MaskWord<PX>::T w = 0;
         if (f.mask) {
-            typename MaskWord<PX>::T w = 0;
 #pragma unroll
             for (int k = 0; k < PX; ++k) w |= (typename MaskWord<PX>::T)mk[k] << (8 * k);
-            store_stream(store_base(f.mask) +
-                                 ((unsigned)r * (unsigned)f.mask_pitch + (unsigned)col),
-                             w);
         }
+        if (col + PX <= f.W && r < rend) {
+            store_stream(o + off, ox);
+            store_stream(o + plane + off, oy);
+            store_stream(o + 2 * plane + off, oz);
+            if (f.mask) store_stream(store_base(f.mask) + moff, w);
+        }
+        if constexpr (PX > 1)
+            if (tail.any && tail.skip > 0 && r < rend) {
+                store_front<OT>(o + off, ox, tail.skip);
+                store_front<OT>(o + plane + off, oy, tail.skip);
+                store_front<OT>(o + 2 * plane + off, oz, tail.skip);
+                if (f.mask) store_front<uint8_t>(store_base(f.mask) + moff, w, tail.skip);
+            }
     }
 }
 
@@ -970,7 +1038,10 @@ __device__ __forceinline__ void run_tile(const FrameDesc &f, int c0, int r0, int
     const InBuf ib = make_inbuf(f.in, f.in_pitch, f.H, esz);
     InBuf rgbb{};
     if constexpr (OUT == OUT_RGBN) rgbb = make_inbuf(f.rgb, f.rgb ? f.rgb_pitch : 0, f.H, 1);
-    const int col_off = col < f.W ? col * esz : kOOB;
+    // (a frame narrower than PX columns is never given PX columns per lane)
+    const Tail tail{PX > 1 && c0 + kLanes * PX > f.W && f.W % PX != 0,
+                    col < f.W ? max(col + PX - f.W, 0) : 0};
+    const int col_off = col < f.W ? (col - tail.skip) * esz : kOOB;
     int hcol = -1;
     if (llane == 0) hcol = c0 - 1;
     if (llane == kLanes - 1) hcol = c0 + kLanes * PX;
@@ -983,9 +1054,9 @@ __device__ __forceinline__ void run_tile(const FrameDesc &f, int c0, int r0, int
     RawRow<KIND, PX> p0;
     RowState<PX> A, B, C;
     load_raw<KIND, PX>(ib, rb - 1, col_off, halo_off, p0);
-    finish_row<KIND, PX, HALF, GK == GK_FD, LEN>(p0, A.row, e);
+    finish_row<KIND, PX, HALF, GK == GK_FD, LEN>(p0, A.row, e, tail);
     load_raw<KIND, PX>(ib, rb, col_off, halo_off, p0);
-    finish_row<KIND, PX, HALF, GK == GK_FD, LEN>(p0, B.row, e);
+    finish_row<KIND, PX, HALF, GK == GK_FD, LEN>(p0, B.row, e, tail);
     if constexpr (LEN && GK == GK_3ROW) {  // the lenient rule's shared horizontal lines
         lenient_hlines<KIND, PX>(A.row);
         lenient_hlines<KIND, PX>(B.row);
@@ -994,7 +1065,7 @@ __device__ __forceinline__ void run_tile(const FrameDesc &f, int c0, int r0, int
     load_raw<KIND, PX>(ib, rb + 1, col_off, halo_off, p0);
 #define SNE_ROW(I, P, X, Y, Z)                                                                  \
     tile_row<KIND, GK, AGG, OUT, PX, HALF, LEN>(f, ib, rgbb, rb + (I), rend, col, col_off, halo_off, \
-                                                e, gw, P, X, Y, Z)
+                                                e, tail, gw, P, X, Y, Z)
 #if SNE_PREFETCH_ROWS == 1
     for (int i = 0; i < n; i += 3) {
         SNE_ROW(i, p0, A, B, C);

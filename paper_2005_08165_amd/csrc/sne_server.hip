@@ -170,10 +170,7 @@ public:
         const size_t oe = out_elem(cfg.out_type);
         int px = tile.px;
         for (auto *q : b.reqs) {
-            uint8_t *out = arena + q->out_offset;
-            uint8_t *mask = out + 3 * (size_t)q->H * q->W * oe;
-            px = std::min(px, max_px(q->in, out, mask, q->W, q->in_pitch, q->W, q->W, 0, 0, 0,
-                                     (int64_t)q->H * q->W, cfg.kind, cfg.out_type));
+            px = std::min(px, max_px(q->in, arena + q->out_offset, q->W, cfg.kind, cfg.out_type));
         }
         TileChoice t = tile;
         t.px = px;
