@@ -140,6 +140,10 @@ int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 // 3 % of it everywhere.
 TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, const Variant &v,
                         bool uneven) {
+    // packed pixels: 16 bytes each, so 2 columns and 4 rows have as much to
+    // store as 4 and 8 of the planes (64 x 480x640 FP32 Sobel-median: 2 x 4
+    // rows 89 us, 4 x 4 94, 1 x 8 96; 70 x 238x494 FP16 Sobel-mean: 34, 37, 36)
+    if (v.out == OUT_RGBN) return TileChoice{std::min(pxmax, 2), 4, kChunkOrder, 0};
     TileChoice best{1, 4, kChunkOrder, 0};
     double best_cost = 0.0;
     const int widest = (v.kind & SNE_LENIENT) ? std::min(pxmax, 2) : pxmax;
@@ -378,20 +382,12 @@ int uniform_impl(sne_ctx *ctx, const void *in, int32_t B, int32_t H, int32_t W, 
         if (hipSetDevice(ctx->device) != hipSuccess) return SNE_ERR_HIP;
         return launch_wide(v, w, (hipStream_t)stream) == hipSuccess ? SNE_OK : SNE_ERR_HIP;
     }
-    int pxmax = max_px(in, normals, W, kind, packed ? SNE_OUT_F16 : out_type);
-    if (packed)  // the packed branch stores whole lanes only
-        while (W % pxmax) pxmax >>= 1;
+    const int pxmax = max_px(in, normals, W, kind, packed ? SNE_OUT_F16 : out_type);
     const int64_t orow = packed ? 16 * out_pitch : out_pitch * (int64_t)out_elem(out_type);
     const int layout =
         row_layout(in, in_pitch * (int64_t)in_elem(kind), in_fs * (int64_t)in_elem(kind)) &&
         row_layout(normals, orow, out_fs * (packed ? 2 : (int64_t)out_elem(out_type)));
     TileChoice t = force ? *force : pick_tile(ctx, H, W, B, v, pxmax, false, layout);
-    // The packed pixels are 16 bytes each: with one column per lane a store
-    // instruction covers 1 KiB of contiguous output, with more columns per
-    // lane it scatters 16-byte pieces (measured 3.6x slower at 4 columns).
-    // Plain block order: 4 % faster than one tile range per XCD with inputs
-    // streamed from HBM.
-    if (packed && !force && !(ctx && ctx->forced.rows > 0)) t = TileChoice{1, 8, 0, 0};
     if (t.px > pxmax || t.rows < 1) return SNE_ERR_ARG;
     v.px = kernel_px(t);
     UniformArgs a;

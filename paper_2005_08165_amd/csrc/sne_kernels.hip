@@ -77,11 +77,6 @@
 #define SNE_BATCH_OCCUPANCY
 #endif
 
-// Packed output stores: 1 = ordinary (cached) stores, 0 = nontemporal.
-#ifndef SNE_RGBN_TEMPORAL
-#define SNE_RGBN_TEMPORAL 0
-#endif
-
 // Rows whose loads are in flight while a row is computed (1 or 2).
 #ifndef SNE_PREFETCH_ROWS
 #define SNE_PREFETCH_ROWS 1
@@ -798,10 +793,13 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
     // packed output: this row's RGBX bytes, in flight while the row is
     // computed (a frame without colour has an empty resource: zeros)
     Vec<float, PX> rgbx;
-    if constexpr (OUT == OUT_RGBN)
+    if constexpr (OUT == OUT_RGBN) {
         rgbx = buf_load<float, PX>(
-            rgbb, (int)((unsigned)r * (unsigned)rgbb.pitch_bytes + (unsigned)(col_off < kOOB
-                                                                             ? col * 4 : kOOB)));
+            rgbb, (int)((unsigned)r * (unsigned)rgbb.pitch_bytes +
+                        (unsigned)(col_off < kOOB ? (col - tail.skip) * 4 : kOOB)));
+        if constexpr (PX > 1)
+            if (tail.any) shift_down<PX>(rgbx, tail.skip);
+    }
     make_middle<KIND, AGG, PX, FD, LEN>(cur.row);
     make_pairs<KIND, AGG, LEN, PX>(cur.row, next.row, cur.below);
     const Row<PX> &rp = prev.row, &rc = cur.row, &rn = next.row;
@@ -964,33 +962,60 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
     for (int k = 0; k < PX; ++k) oz.v[k] = Out<OUT>::cvt(fz[k]);
     if constexpr (OUT == OUT_RGBN) {
         // one 16-byte pixel: R, G, B (bytes / 255), mask, n_x, n_y, n_z, 0
-        if (col < f.W && r < rend) {
-            SNE_GLOBAL char *o = store_base(f.out) +
-                      ((unsigned)r * (unsigned)f.out_pitch + (unsigned)col) * 16u;
+        typedef unsigned U4 __attribute__((ext_vector_type(4)));
+        U4 px[PX];
 #pragma unroll
-            for (int k = 0; k < PX; ++k) {
-                const unsigned c = __builtin_bit_cast(unsigned, rgbx.v[k]);
-                const float s255 = 1.f / 255.f;
-                const _Float16 R = Out<OUT_F16>::cvt((float)(c & 0xffu) * s255);
-                const _Float16 G = Out<OUT_F16>::cvt((float)((c >> 8) & 0xffu) * s255);
-                const _Float16 Bc = Out<OUT_F16>::cvt((float)((c >> 16) & 0xffu) * s255);
-                const _Float16 M = mk[k] ? (_Float16)1.f : (_Float16)0.f;
-                typedef _Float16 H8 __attribute__((ext_vector_type(8)));
-                const H8 px = {R, G, Bc, M, ox.v[k], oy.v[k], oz.v[k], (_Float16)0.f};
-#if SNE_RGBN_TEMPORAL
-                *(SNE_GLOBAL H8 *)(o + 16 * k) = px;
-#else
-                store_stream(o + 16 * k, px);
-#endif
-            }
-            if (f.mask) {
-                typename MaskWord<PX>::T w = 0;
+        for (int k = 0; k < PX; ++k) {
+            const unsigned c = __builtin_bit_cast(unsigned, rgbx.v[k]);
+            const float s255 = 1.f / 255.f;
+            const _Float16 R = Out<OUT_F16>::cvt((float)(c & 0xffu) * s255);
+            const _Float16 G = Out<OUT_F16>::cvt((float)((c >> 8) & 0xffu) * s255);
+            const _Float16 Bc = Out<OUT_F16>::cvt((float)((c >> 16) & 0xffu) * s255);
+            const _Float16 M = mk[k] ? (_Float16)1.f : (_Float16)0.f;
+            typedef _Float16 H8 __attribute__((ext_vector_type(8)));
+            px[k] = __builtin_bit_cast(U4, H8{R, G, Bc, M, ox.v[k], oy.v[k], oz.v[k],
+                                              (_Float16)0.f});
+        }
+        // A lane's pixels are 16 PX contiguous bytes, but one store
+        // instruction would scatter 16-byte pieces 16 PX bytes apart (3.6
+        // times slower at 4 columns).  Each wavefront turns its row around
+        // through LDS, so that a store covers kLanes contiguous pixels.
+        // Slots are swizzled by lane so that neither direction has bank
+        // conflicts.  One wavefront uses each part: no barrier, only order.
+        // 64 x 480x640 with colour (24 bytes a pixel): 89 us at 2 columns,
+        // 5.3 TB/s, against 98 us at 1 column without the turn.
+        constexpr int kLanes = HALF ? kWave / 2 : kWave;
+        const int llane = (int)threadIdx.x & (kLanes - 1), c0 = col - llane * PX;
+        const unsigned row = (unsigned)r * (unsigned)f.out_pitch;
+        SNE_GLOBAL char *o = store_base(f.out);
+        if constexpr (PX == 1) {
+            if (col < f.W && r < rend) store_stream(o + (row + (unsigned)col) * 16u, px[0]);
+        } else {
+            __shared__ U4 turn[kBlock * PX];
+            U4 *part = turn + ((int)threadIdx.x - llane) * PX;
+            auto slot = [](int l, int k) { return l * PX + (k ^ ((l * PX / 16) & (PX - 1))); };
+            asm volatile("" ::: "memory");
 #pragma unroll
-                for (int k = 0; k < PX; ++k) w |= (typename MaskWord<PX>::T)mk[k] << (8 * k);
-                store_stream(store_base(f.mask) +
-                                 ((unsigned)r * (unsigned)f.mask_pitch + (unsigned)col),
-                             w);
+            for (int k = 0; k < PX; ++k) part[slot(llane, k)] = px[k];
+            __builtin_amdgcn_wave_barrier();
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int j = 0; j < PX; ++j) {
+                const int v = j * kLanes + llane;
+                const U4 q = part[slot(v / PX, v % PX)];
+                if (c0 + v < f.W && r < rend)
+                    store_stream(o + (row + (unsigned)(c0 + v)) * 16u, q);
             }
+        }
+        if (f.mask) {
+            typename MaskWord<PX>::T w = 0;
+#pragma unroll
+            for (int k = 0; k < PX; ++k) w |= (typename MaskWord<PX>::T)mk[k] << (8 * k);
+            SNE_GLOBAL char *m =
+                store_base(f.mask) + ((unsigned)r * (unsigned)f.mask_pitch + (unsigned)col);
+            if (col + PX <= f.W && r < rend) store_stream(m, w);
+            if constexpr (PX > 1)
+                if (tail.any && tail.skip > 0 && r < rend) store_front<uint8_t>(m, w, tail.skip);
         }
     } else {
         // uniform plane bases + one 32-bit byte offset per lane (the host

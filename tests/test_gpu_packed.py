@@ -66,3 +66,33 @@ def test_packed_without_colour_and_single_frame():
     assert torch.equal(pk[..., 4:7].permute(2, 0, 1).contiguous().view(torch.int16),
                        n16.view(torch.int16))
     assert torch.equal(pk[..., 3], m16.to(torch.float16))
+
+
+@pytest.mark.parametrize("kind", ["depth_f32", "depth_u16+lenient", "disparity_f32"])
+def test_packed_tile_shapes_and_widths_bitwise(kind):
+    """Every tile shape turns the same pixels around: equal to 1 column per
+    lane, for widths that cut the last lane, a pitch larger than the width and
+    rows the tile does not divide; nothing outside the frame is written."""
+    base = kind.partition("+")[0]
+    K, H, B = (300.0, 300.0, 130.0, 6.0), 13, 2
+    rng = np.random.default_rng(7500)
+    ctx = sne.Context(0, tuning=False)
+    for W, pad in ((1, 0), (3, 1), (64, 0), (130, 3), (257, 0), (515, 2)):
+        z = 2.0 + 0.3 * rng.random((B, H, W))
+        z[rng.random(z.shape) < 0.1] = 0
+        raw = torch.from_numpy((z * 1000).astype(np.uint16) if base == "depth_u16"
+                               else z.astype(np.float32)).cuda()
+        rgb = torch.from_numpy(rng.integers(0, 256, size=(B, H, W, 4), dtype=np.uint8)).cuda()
+        ref = None
+        for px, rows, lanes in ((1, 4, 64), (1, 3, 32), (2, 5, 64), (2, 4, 32), (4, 4, 64),
+                                (4, 3, 32)):
+            ctx.set_tile(px, rows, lanes)
+            out = torch.full((B, H, W + pad, 8), 7.0, dtype=torch.float16, device="cuda")
+            msk = torch.full((B, H, W), 9, dtype=torch.uint8, device="cuda")
+            sne.estimate_rgbn(raw, K, kind, "sobel", "median", rgb=rgb, out=out[:, :, :W],
+                              mask=msk, ctx=ctx)
+            got = (out.view(torch.int16).cpu(), msk.cpu())
+            assert (out[:, :, W:] == 7).all() and (msk < 2).all()
+            ref = ref or got
+            for a, b in zip(ref, got):
+                assert torch.equal(a, b), (kind, W, pad, px, rows, lanes)
