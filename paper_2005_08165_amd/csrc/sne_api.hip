@@ -187,20 +187,19 @@ TileChoice pick_tile(const sne_ctx *ctx, int H, int W, int64_t B, const Variant 
     if (ctx) {
         // a shape tuned on this row layout, else (aligned rows) one tuned on
         // unaligned rows; an uneven batch prefers a shape tuned on the
-        // persistent kernel; a shape tuned for the variant itself, else
-        // (lenient rule) the one tuned for the strict rule of the same variant
+        // persistent kernel.  The lenient rule has entries of its own only:
+        // its kernels want fewer columns than the strict ones (default_tile)
         for (int lay : {layout, 0}) {
             if (lay != layout && layout == 0) break;
-            for (int kind : {v.kind, base_kind(v.kind)})
-                for (int bc : {uneven ? kUnevenClass : -1, batch_class(B)}) {
-                    if (bc < 0) continue;
-                    auto it = ctx->cache.find(TileKey{H, W, bc, kind, v.grad, v.agg, v.out, lay});
-                    if (it != ctx->cache.end()) {
-                        TileChoice t = it->second;
-                        while (t.px > pxmax) t.px >>= 1;
-                        return t;
-                    }
+            for (int bc : {uneven ? kUnevenClass : -1, batch_class(B)}) {
+                if (bc < 0) continue;
+                auto it = ctx->cache.find(TileKey{H, W, bc, v.kind, v.grad, v.agg, v.out, lay});
+                if (it != ctx->cache.end()) {
+                    TileChoice t = it->second;
+                    while (t.px > pxmax) t.px >>= 1;
+                    return t;
                 }
+            }
             if (layout == 0) break;
         }
     }

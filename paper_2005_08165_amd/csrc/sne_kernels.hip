@@ -358,21 +358,31 @@ template <int KIND, int PX> __device__ __forceinline__ void make_hdiff(Row<PX> &
     }
 }
 
+// A sample as the window holds it.  Strict rule: as it is (the masks say
+// whether it counts).  Lenient rule: an invalid one is 0 for the mean, which
+// multiplies it by the pair's reciprocal 0, and NaN for the median, so that
+// one ordered compare with the centre leaves it out.
+template <int KIND, int AGG, bool LEN>
+__device__ __forceinline__ float sample(typename Raw<KIND>::T x) {
+    if constexpr (!LEN) return Raw<KIND>::window(x);
+    if constexpr (AGG == AGG_MEAN) return Raw<KIND>::value(x);
+    return Raw<KIND>::ok(x) ? Raw<KIND>::window(x) : __builtin_nanf("");
+}
+
 // A row's values and validity, and for the 3-row filters its horizontal
 // differences (FD needs only those of the middle row: make_middle).
-template <int KIND, int PX, bool HALF, bool FD, bool LEN>
+template <int KIND, int AGG, int PX, bool HALF, bool FD, bool LEN>
 __device__ __forceinline__ void finish_row(RawRow<KIND, PX> &raw, Row<PX> &o,
                                            const Edges &e, const Tail &tail) {
     if constexpr (PX > 1)
         if (tail.any) shift_down<PX>(raw.x, tail.skip);
     // lanes that take their outer neighbour from the halo sample
     constexpr Mask kLeft = HALF ? 0x100000001ull : 1ull, kRight = kLeft << (HALF ? 31 : 63);
-    // the lenient mean multiplies invalid neighbours by 0: they must be finite
-    const float h = LEN ? Raw<KIND>::value(raw.h) : Raw<KIND>::window(raw.h);
+    const float h = sample<KIND, AGG, LEN>(raw.h);
     const Mask okh = mask_of(Raw<KIND>::ok(raw.h));
 #pragma unroll
     for (int k = 0; k < PX; ++k) {
-        o.z[k + 1] = LEN ? Raw<KIND>::value(raw.x.v[k]) : Raw<KIND>::window(raw.x.v[k]);
+        o.z[k + 1] = sample<KIND, AGG, LEN>(raw.x.v[k]);
         o.ok[k + 1] = mask_of(Raw<KIND>::ok(raw.x.v[k]));
     }
     o.z[0] = left_of<HALF>(h, o.z[PX], e);
@@ -553,14 +563,14 @@ __device__ __forceinline__ void candidates(const float (&Nj)[8], const float (&r
 // normal.
 // A neighbour gives no candidate when its raw value equals the centre's
 // (dZ = 0) or, under the lenient rule, when it is invalid.
-template <bool LEN> __device__ __forceinline__ bool left_out(float zj, float zc, Mask okj) {
-    if constexpr (LEN) return lane(mask_of(zj == zc) | ~okj);
+template <bool LEN> __device__ __forceinline__ bool left_out(float zj, float zc) {
+    if constexpr (LEN) return !__builtin_islessgreater(zj, zc);  // invalid: NaN
     return zj == zc;
 }
 
 template <int KIND, bool LEN>
 __device__ __forceinline__ float median8(const float (&Nj)[8], const float (&rj)[8],
-                                         const float (&zj)[8], const Mask (&okj)[8], float zc, float B, bool general) {
+                                         const float (&zj)[8], float zc, float B, bool general) {
     float t[8];
     candidates<KIND>(Nj, rj, zc, t);
     const float half = KIND == KIND_DISP ? -0.5f * zc : 0.5f;
@@ -568,7 +578,7 @@ __device__ __forceinline__ float median8(const float (&Nj)[8], const float (&rj)
     float pad = kInf;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const bool drop = left_out<LEN>(zj[j], zc, okj[j]);
+        const bool drop = left_out<LEN>(zj[j], zc);
         t[j] = drop ? pad : t[j];
         pad = drop ? -pad : pad;
     }
@@ -607,14 +617,14 @@ __device__ __forceinline__ float finish_mean(float sum, float weight, float zc, 
 }
 template <int KIND, bool LEN>
 __device__ __forceinline__ float mean8(float Gu, float Gv, const float (&rj)[8],
-                                       const float (&zj)[8], const Mask (&okj)[8], float zc,
+                                       const float (&zj)[8], float zc,
                                        float B, bool general) {
     if (!general) return finish_mean<KIND>(slot_sum<KIND>(Gu, Gv, rj, zj), 0.125f, zc, B);
     float r[8];
     int m = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const bool drop = left_out<LEN>(zj[j], zc, okj[j]);
+        const bool drop = left_out<LEN>(zj[j], zc);
         r[j] = drop ? 0.f : rj[j];
         m += drop ? 0 : 1;
     }
@@ -748,8 +758,6 @@ __device__ __forceinline__ float normal_z(int k, const FrameDesc &f, int col, fl
                          rn.z[c + 1], rp.z[c - 1], rn.z[c - 1], rp.z[c + 1]};
     const float rj[8] = {rc.rE[c], -rc.rE[c - 1], pd.rS[k], -pu.rS[k],
                          pd.rSE[c], -pu.rSE[k], pd.rSW[k], -pu.rSW[c]};
-    const Mask okj[8] = {rc.ok[c + 1], rc.ok[c - 1], rn.ok[c],     rp.ok[c],
-                         rn.ok[c + 1], rp.ok[c - 1], rn.ok[c - 1], rp.ok[c + 1]};
     if constexpr (kPairMean<KIND, AGG, LEN>) {
         int m = pu.top[k];
         m += lane(rc.kE[c]) ? 1 : 0;
@@ -767,11 +775,11 @@ __device__ __forceinline__ float normal_z(int k, const FrameDesc &f, int col, fl
         }
         return finish_mean<KIND>(sum, rcp((float)m), zc, B);
     } else if constexpr (AGG == AGG_MEAN) {
-        return mean8<KIND, LEN>(Gu, Gv, rj, zj, okj, zc, B, GENERAL);
+        return mean8<KIND, LEN>(Gu, Gv, rj, zj, zc, B, GENERAL);
     } else {
         const float Spp = Gu + Gv, Spm = Gu - Gv;
         const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};
-        return median8<KIND, LEN>(Nj, rj, zj, okj, zc, B, GENERAL);
+        return median8<KIND, LEN>(Nj, rj, zj, zc, B, GENERAL);
     }
 }
 
@@ -787,7 +795,7 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
                                          RowState<PX> &next) {
     constexpr bool FD = GK == GK_FD;
     constexpr bool LENR = LEN && GK != GK_CUSTOM;  // the lenient rule applies
-    finish_row<KIND, PX, HALF, FD, LEN>(pend, next.row, e, tail);
+    finish_row<KIND, AGG, PX, HALF, FD, LEN>(pend, next.row, e, tail);
     if constexpr (LENR && !FD) lenient_hlines<KIND, PX>(next.row);
     load_raw<KIND, PX>(ib, r + 1 + SNE_PREFETCH_ROWS, col_off, halo_off, pend);  // prefetch
     // packed output: this row's RGBX bytes, in flight while the row is
@@ -889,9 +897,13 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
                                            V[c], rp.ok[c], rc.ok[c], rn.ok[c], vc);
                 valid[k] = rc.ok[c] & hc & vc;
             }
-        } else if constexpr (LENR) {
-            if (lenient_path) {
-                general[k] = true;
+        }
+    }
+    if constexpr (LENR && !FD) {
+        if (lenient_path) {
+#pragma unroll
+            for (int k = 0; k < PX; ++k) {
+                const int c = k + 1;
                 Mask du, dv;
                 Gu[k] = lenient_combine(rc.Lh[k], rc.hh[k], rp.Lh[k], rp.hh[k], rn.Lh[k],
                                         rn.hh[k], gw, du);
@@ -903,29 +915,48 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
     }
     const float fv = (float)r - f.v0;
     float nz[PX];
+    bool done = false;
+    if constexpr (LENR && !FD && !kTieHeavy<KIND> && !kPairMean<KIND, AGG, LEN>) {
+        // one branch for the row: no test of its pixels' ties
+        if (lenient_path) {
+            float unused;
 #pragma unroll
-    for (int k = 0; k < PX; ++k) {
-        // A slot is left out iff raw_j == raw, i.e. its pair reciprocal is
-        // +-inf.  That is rare in FP32 data: pad only when a valid pixel of
-        // this wavefront needs it (the choice is wave-uniform, and both paths
-        // give the same result when nothing is left out).
-        // (signs do not matter here: the raw pair values are used)
-        if constexpr (!kTieHeavy<KIND> && !kPairMean<KIND, AGG, LEN>) {
-            const int c = k + 1;
-            const float rmax = vmax8abs(rc.rE[c], rc.rE[c - 1], pd.rS[k], pu.rS[k], pd.rSE[c],
-                                        pu.rSE[k], pd.rSW[k], pu.rSW[c]);
-            general[k] = general[k] || (mask_of(rmax == kInf) & valid[k]) != 0;
+            for (int k = 0; k < PX; ++k) {
+                // values of their own: otherwise the compiler forms the
+                // candidates ahead of the branch, for both sides of it, and
+                // holds those of all pixels at once
+                asm("" : "+v"(Gu[k]), "+v"(Gv[k]));
+                nz[k] = normal_z<KIND, AGG, LEN, true, PX>(k, f, col, fv, Gu[k], Gv[k], unused, rp,
+                                                           rc, rn, pu, pd);
+            }
         }
-        float scale = 1.f;
-        if (general[k])
-            nz[k] = normal_z<KIND, AGG, LEN, true, PX>(k, f, col, fv, Gu[k], Gv[k], scale, rp, rc,
-                                                       rn, pu, pd);
-        else
-            nz[k] = normal_z<KIND, AGG, LEN, false, PX>(k, f, col, fv, Gu[k], Gv[k], scale, rp, rc,
-                                                        rn, pu, pd);
-        if constexpr (kTieHeavy<KIND> && kPairMean<KIND, AGG, LEN>) {
-            Gu[k] *= scale;
-            Gv[k] *= scale;
+        done = lenient_path;
+    }
+    if (!done) {
+#pragma unroll
+        for (int k = 0; k < PX; ++k) {
+            // A slot is left out iff raw_j == raw, i.e. its pair reciprocal is
+            // +-inf.  That is rare in FP32 data: pad only when a valid pixel of
+            // this wavefront needs it (the choice is wave-uniform, and both paths
+            // give the same result when nothing is left out).
+            // (signs do not matter here: the raw pair values are used)
+            if constexpr (!kTieHeavy<KIND> && !kPairMean<KIND, AGG, LEN>) {
+                const int c = k + 1;
+                const float rmax = vmax8abs(rc.rE[c], rc.rE[c - 1], pd.rS[k], pu.rS[k], pd.rSE[c],
+                                            pu.rSE[k], pd.rSW[k], pu.rSW[c]);
+                general[k] = general[k] || (mask_of(rmax == kInf) & valid[k]) != 0;
+            }
+            float scale = 1.f;
+            if (general[k])
+                nz[k] = normal_z<KIND, AGG, LEN, true, PX>(k, f, col, fv, Gu[k], Gv[k], scale, rp, rc,
+                                                           rn, pu, pd);
+            else
+                nz[k] = normal_z<KIND, AGG, LEN, false, PX>(k, f, col, fv, Gu[k], Gv[k], scale, rp, rc,
+                                                            rn, pu, pd);
+            if constexpr (kTieHeavy<KIND> && kPairMean<KIND, AGG, LEN>) {
+                Gu[k] *= scale;
+                Gv[k] *= scale;
+            }
         }
     }
 
@@ -1053,8 +1084,14 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
 // times with the window's roles rotating, so no register state is copied.
 template <int KIND, int GK, int AGG, int OUT, int PX, bool HALF, bool LEN>
 __device__ __forceinline__ void run_tile(const FrameDesc &f, int c0, int r0, int rows,
-                                         const GradW &gw) {
+                                         const GradW &kgw) {
     using T = typename Raw<KIND>::T;
+    // The lenient rule selects among the rescaling factors per lane; left in
+    // the kernel arguments, the select becomes one of their addresses and a
+    // memory load per pixel.
+    GradW gw = kgw;
+    if constexpr (LEN)
+        asm("" : "+s"(gw.r[0]), "+s"(gw.r[1]), "+s"(gw.r[2]), "+s"(gw.r[3]));
     constexpr int kLanes = HALF ? kWave / 2 : kWave;
     const int lane = threadIdx.x & (kWave - 1);
     const int llane = lane & (kLanes - 1);
@@ -1079,9 +1116,9 @@ __device__ __forceinline__ void run_tile(const FrameDesc &f, int c0, int r0, int
     RawRow<KIND, PX> p0;
     RowState<PX> A, B, C;
     load_raw<KIND, PX>(ib, rb - 1, col_off, halo_off, p0);
-    finish_row<KIND, PX, HALF, GK == GK_FD, LEN>(p0, A.row, e, tail);
+    finish_row<KIND, AGG, PX, HALF, GK == GK_FD, LEN>(p0, A.row, e, tail);
     load_raw<KIND, PX>(ib, rb, col_off, halo_off, p0);
-    finish_row<KIND, PX, HALF, GK == GK_FD, LEN>(p0, B.row, e, tail);
+    finish_row<KIND, AGG, PX, HALF, GK == GK_FD, LEN>(p0, B.row, e, tail);
     if constexpr (LEN && GK == GK_3ROW) {  // the lenient rule's shared horizontal lines
         lenient_hlines<KIND, PX>(A.row);
         lenient_hlines<KIND, PX>(B.row);
@@ -1316,9 +1353,8 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
             const float rmax = vmax8abs(rj[0], rj[1], rj[2], rj[3], rj[4], rj[5], rj[6], rj[7]);
             general = __builtin_amdgcn_ballot_w64(valid && !(rmax < kInf)) != 0;
         }
-        const Mask okj[8] = {};  // strict rule: not looked at
-        const float nz = (AGG == AGG_MEAN) ? mean8<KIND, false>(Gu, Gv, rj, zj, okj, z0, B, general)
-                                           : median8<KIND, false>(Nj, rj, zj, okj, z0, B, general);
+        const float nz = (AGG == AGG_MEAN) ? mean8<KIND, false>(Gu, Gv, rj, zj, z0, B, general)
+                                           : median8<KIND, false>(Nj, rj, zj, z0, B, general);
         const float nx = f.fx * Gu, ny = f.fy * Gv;
         const float n2 = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
         const bool deg = !(n2 > 0.f);
