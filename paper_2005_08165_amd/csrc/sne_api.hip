@@ -359,7 +359,7 @@ int uniform_impl(sne_ctx *ctx, const void *in, int32_t B, int32_t H, int32_t W, 
         return SNE_ERR_UNSUPPORTED;
     Variant v{kind, grad, agg, packed ? (int)OUT_RGBN : out_type, 1};
     if (custom && ctx->custom_n > 3) {
-        // a 5x5 or 7x7 filter: the LDS-tiled kernel, one block per 64 x 16 tile
+        // a 5x5 or 7x7 filter: the LDS-tiled kernel, one block per 128 x 16 tile
         WideArgs w;
         w.f = make_desc(in, normals, mask, H, W, in_pitch, out_pitch, mask_pitch, *K);
         w.in_fstride = in_fs;

@@ -61,8 +61,8 @@ struct UniformArgs {
 };
 
 // Wide custom gradient filters: a (2R+1)x(2R+1) K_x (R = 2, 3; K_y = K_x^T)
-// over a uniform batch, one block per 64 x 16 output tile of a frame.
-constexpr int kWideTW = 64, kWideTH = 16;  // output tile; 4 rows per thread
+// over a uniform batch, one block per 128 x 16 output tile of a frame.
+constexpr int kWideTW = 128, kWideTH = 16;  // output tile; 2 x 4 pixels per thread
 constexpr int kWideMaxN = 7;
 struct WideArgs {
     FrameDesc f;

@@ -1211,31 +1211,49 @@ __global__ __launch_bounds__(kBlock) SNE_OCCUPANCY void sne_uniform_kernel(Unifo
 // ------------------------------------------------ wide custom gradient filters
 // A (2R+1)x(2R+1) custom K_x (R = 2, 3; K_y = K_x^T) reads R samples on each
 // side, more than the three-row register window holds.  One block stages a
-// 64 x 16 output tile and its R-wide apron in LDS as (z, s) pairs (z = 0
-// where invalid or outside the frame), then each thread takes a column of 4
-// pixels.  The taps are formed against one reference sample of the column
-// (its second pixel, inside the window of every pixel of the column):
+// 128 x 16 output tile and its R-wide apron in LDS as (z, s) pairs (z = 0
+// where invalid or outside the frame), then each thread takes 2 columns by 4
+// rows of pixels.  The taps are formed against one reference sample of the
+// thread's pixels, inside the window of every one of them:
 // sum_ab K_ab s_ab = sum_ab K_ab (s_ab - s_r) + (sum K) s_r, with
 // s_ab - s_r = (z_r - z_ab) s_ab s_r from a raw-value difference (for
-// disparity d_ab - d_r), so each sample's difference serves all 4 pixels:
+// disparity d_ab - d_r), so each sample's difference serves all 8 pixels:
 //   G = s_r (sum_ab K_ab (z_r - z_ab) s_ab + sum K)      (depth)
 //   G = sum_ab K_ab (d_ab - d_r) + (sum K) d_r            (disparity)
 // The neighbourhood of n_z stays the 8-connected one, and a pixel is kept iff
 // its whole (2R+1)x(2R+1) window is inside the frame and valid.
 // SEP: K_x = kc kr^T (a smoothing column times a derivative row, say); then
-// each window row's two weighted sums serve every pixel of the column, so a
-// pixel takes 2(2R+1) FMAs of row sums instead of 2(2R+1)^2 taps.
+// each window row's two weighted sums serve every pixel of a column, so a
+// pixel takes 2(2R+1) FMAs of row sums instead of 2(2R+1)^2 taps.  Its weights
+// are held in vector registers: an FMA with a scalar operand issues at half
+// rate.
+// Bound by instruction issue.  Two columns per thread share the reference's
+// differences, the row minima and the pairs between them (6 instead of 8
+// reciprocals per pixel): 64 x 480x640 FP32 median, 5x5 product 73 us (98
+// with one column), 7x7 product 87 (128 before the series), 5x5 general 79
+// (117).  Tiles of 8 rows, 2 per thread, were no faster where 16-row tiles leave
+// CUs idle (one 480x640 frame 8.6 us with either; 8 frames 13.6 against 12.3).
 // Blocks run in runs of kWideRun per XCD (xcd_chunk), so the tiles above and
 // below a tile mostly share its apron rows through one L2.
 constexpr int kWideRun = 16;
+
+// A scalar weight as a vector register's value.
+__device__ __forceinline__ float in_vgpr(float x) {
+    float r;
+    asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(x));
+    return r;
+}
 
 template <int KIND, int R, int AGG, int OUT, bool SEP>
 __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
     constexpr int N = 2 * R + 1, LW = kWideTW + 2 * R, LH = kWideTH + 2 * R;
     constexpr int RPT = kWideTH / kWavesPerBlock;  // rows per thread
-    static_assert(RPT * kWavesPerBlock == kWideTH && kWideTW == kWave, "tile shape");
-    static_assert(RPT >= 2 && RPT - 2 <= R, "the reference is in every pixel's window");
-    __shared__ float2 T[LH * LW];  // (z, s)
+    constexpr int CPT = kWideTW / kWave;           // columns per thread
+    constexpr int S = N + CPT - 1;                 // samples of a window row
+    static_assert(RPT * kWavesPerBlock == kWideTH && CPT == 2, "tile shape");
+    static_assert(RPT >= 2 && RPT - 2 <= R && CPT - 1 <= R, "the reference is in every window");
+    static_assert(S % 2 == 0 && LW % 2 == 0, "16-byte LDS reads");
+    __shared__ float4 T[LH * LW / 2];  // (z, s) of two columns
     using IT = typename Raw<KIND>::T;
     using OT = typename Out<OUT>::T;
     const int blk = xcd_chunk((int)blockIdx.x, (int)gridDim.x, kWideRun);
@@ -1251,129 +1269,239 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
     if (f.mask) f.mask = a.f.mask + frame * a.mask_fstride;
     const int esz = (int)sizeof(IT);
     const InBuf ib = make_inbuf(f.in, f.in_pitch, f.H, esz);
-    const int lane = (int)threadIdx.x & (kWave - 1), wv = (int)(threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
-    // stage row by row (wavefront wv takes rows wv, wv + 4, ...): lane l holds
-    // column x0 - R + l, lanes below 2R also the apron column x0 + 64 - R + l;
-    // samples outside the frame read as 0 (invalid)
-    const int gx0 = x0 - R + lane, gx1 = gx0 + kWave;
-    const int off0 = gx0 >= 0 && gx0 < f.W ? gx0 * esz : kOOB;
-    const int off1 = lane < 2 * R && gx1 < f.W ? gx1 * esz : kOOB;
-    for (int row = wv; row < LH; row += kWavesPerBlock) {
-        const int gy = y0 - R + row;
+    // stage pairs of columns (gx, gx + 1); samples outside the frame read as 0
+    // (invalid).  Wavefront wv takes rows wv, wv + 4, ... of the first 64
+    // pairs, and the apron pairs right of them go one to a thread; all loads
+    // are issued before the first is used.
+    constexpr int kPasses = (LH + kWavesPerBlock - 1) / kWavesPerBlock;
+    static_assert(LH * R <= kBlock, "one apron pair per thread");
+    IT z0[kPasses + 1], z1[kPasses + 1];
+    auto load_pair = [&](int row, int pair, IT &l, IT &r) {
+        const int gy = y0 - R + row, gx = x0 - R + 2 * pair;
         const bool yin = gy >= 0 && gy < f.H;
-        const int rowb = yin ? gy * ib.pitch_bytes : 0;
-        const float z0 = Raw<KIND>::value(
-            buf_load<IT, 1>(ib, yin && off0 != kOOB ? rowb + off0 : kOOB).v[0]);
-        T[row * LW + lane] = make_float2(z0, KIND == KIND_DISP ? z0 : rcp(z0));
-        if (lane < 2 * R) {
-            const float z1 = Raw<KIND>::value(
-                buf_load<IT, 1>(ib, yin && off1 != kOOB ? rowb + off1 : kOOB).v[0]);
-            T[row * LW + kWave + lane] = make_float2(z1, KIND == KIND_DISP ? z1 : rcp(z1));
-        }
-    }
+        const int at = gy * ib.pitch_bytes + gx * esz;
+        l = buf_load<IT, 1>(ib, yin && gx >= 0 && gx < f.W ? at : kOOB).v[0];
+        r = buf_load<IT, 1>(ib, yin && gx + 1 >= 0 && gx + 1 < f.W ? at + esz : kOOB).v[0];
+    };
+    auto put_pair = [&](int row, int pair, IT l, IT r) {
+        const float zl = Raw<KIND>::value(l), zr = Raw<KIND>::value(r);
+        T[row * (LW / 2) + pair] = make_float4(zl, KIND == KIND_DISP ? zl : rcp(zl), zr,
+                                               KIND == KIND_DISP ? zr : rcp(zr));
+    };
+    const int arow = (int)threadIdx.x / R, apair = kWave + (int)threadIdx.x % R;
+    const bool apron = (int)threadIdx.x < LH * R;
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) load_pair(wv + i * kWavesPerBlock, lane, z0[i], z1[i]);
+    if (apron) load_pair(arow, apair, z0[kPasses], z1[kPasses]);
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i)
+        if (LH % kWavesPerBlock == 0 || wv + i * kWavesPerBlock < LH)
+            put_pair(wv + i * kWavesPerBlock, lane, z0[i], z1[i]);
+    if (apron) put_pair(arow, apair, z0[kPasses], z1[kPasses]);
     __syncthreads();
 
-    const int top = wv * RPT;  // LDS row of pixel 0's window top
-    const int x = x0 + lane;
-    const float2 ref = T[(top + 1 + R) * LW + lane + R];  // pixel 1 of the column
-    float gu[RPT], gv[RPT], mn[RPT];
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-        gu[i] = 0.f;
-        gv[i] = 0.f;
-        mn[i] = kInf;
-    }
-    // window row ar feeds pixel i as its filter row ar - i
-#pragma unroll
-    for (int ar = 0; ar < RPT + 2 * R; ++ar) {
-        float zv[N], d[N];
+    const int top = wv * RPT;  // LDS row of pixel row 0's window top
+    const int x = x0 + CPT * lane;
+    const float4 *base = T + top * (LW / 2) + lane;  // the window's first pair
+    const float4 rf = base[(1 + R) * (LW / 2) + R / 2];
+    const float2 ref = R % 2 ? make_float2(rf.z, rf.w) : make_float2(rf.x, rf.y);
+    float kc[N], kr[N];
+    if constexpr (SEP) {
 #pragma unroll
         for (int b = 0; b < N; ++b) {
-            const float2 t = T[(top + ar) * LW + lane + b];
-            zv[b] = t.x;
-            d[b] = KIND == KIND_DISP ? t.y - ref.y : (ref.x - t.x) * t.y;
+            kc[b] = in_vgpr(a.kc[b]);
+            kr[b] = in_vgpr(a.kr[b]);
         }
-        float rmin = vmin3(zv[0], zv[1], zv[2]);
+    }
+    float gu[RPT][CPT], gv[RPT][CPT], mn[RPT][CPT];
+    float zk[RPT + 2][CPT + 2];  // the 3x3 neighbourhoods
+    float rmin[2][CPT];
 #pragma unroll
-        for (int b = 3; b < N; b += 2)
-            rmin = b + 1 < N ? vmin3(rmin, zv[b], zv[b + 1]) : vmin(rmin, zv[b]);
-        float hr = 0.f, hc = 0.f;  // SEP: sum_b kr[b] d[b], sum_b kc[b] d[b]
+    for (int i = 0; i < RPT; ++i)
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            gu[i][c] = 0.f;
+            gv[i][c] = 0.f;
+            mn[i][c] = kInf;
+        }
+    // window row ar feeds pixel row i as its filter row ar - i
+#pragma unroll
+    for (int ar = 0; ar < RPT + 2 * R; ++ar) {
+        // one window row at a time: left alone, the scheduler reads them all
+        // first and takes 136 registers
+        __builtin_amdgcn_sched_barrier(0);
+        float zv[S], d[S];
+#pragma unroll
+        for (int b = 0; b < S; b += 2) {
+            const float4 t = base[ar * (LW / 2) + b / 2];
+            zv[b] = t.x;
+            zv[b + 1] = t.z;
+            d[b] = KIND == KIND_DISP ? t.y - ref.y : (ref.x - t.x) * t.y;
+            d[b + 1] = KIND == KIND_DISP ? t.w - ref.y : (ref.x - t.z) * t.w;
+        }
+        if (ar >= R - 1 && ar <= R + RPT) {
+#pragma unroll
+            for (int c = 0; c < CPT + 2; ++c) zk[ar - (R - 1)][c] = zv[R - 1 + c];
+        }
+        // minima of the row's two windows: zv[1..2R] is common
+        float both = vmin3(zv[1], zv[2], zv[3]);
+#pragma unroll
+        for (int b = 4; b + 1 <= 2 * R; b += 2)
+            if (b + 1 < 2 * R) both = vmin3(both, zv[b], zv[b + 1]);
+        rmin[ar & 1][0] = vmin3(both, zv[0], zv[2 * R]);
+        rmin[ar & 1][1] = vmin3(both, zv[2 * R], zv[2 * R + 1]);
+        if (ar & 1) {  // two rows at a time into the windows that hold them
+#pragma unroll
+            for (int i = 0; i < RPT; ++i)
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) {
+                    const bool h0 = ar - 1 >= i && ar - 1 <= i + 2 * R;
+                    const bool h1 = ar >= i && ar <= i + 2 * R;
+                    if (h0 && h1) mn[i][c] = vmin3(mn[i][c], rmin[0][c], rmin[1][c]);
+                    else if (h0) mn[i][c] = vmin(mn[i][c], rmin[0][c]);
+                    else if (h1) mn[i][c] = vmin(mn[i][c], rmin[1][c]);
+                }
+        }
+        float hr[CPT], hc[CPT];  // SEP: sum_b kr[b] d[b], sum_b kc[b] d[b]
         if constexpr (SEP) {
 #pragma unroll
-            for (int b = 0; b < N; ++b) {
-                hr = fmaf(a.kr[b], d[b], hr);
-                hc = fmaf(a.kc[b], d[b], hc);
+            for (int c = 0; c < CPT; ++c) {
+                hr[c] = 0.f;
+                hc[c] = 0.f;
+#pragma unroll
+                for (int b = 0; b < N; ++b) {
+                    hr[c] = fmaf(kr[b], d[b + c], hr[c]);
+                    hc[c] = fmaf(kc[b], d[b + c], hc[c]);
+                }
             }
         }
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
             const int ka = ar - i;
             if (ka < 0 || ka > 2 * R) continue;
-            mn[i] = vmin(mn[i], rmin);
-            if constexpr (SEP) {
-                gu[i] = fmaf(a.kc[ka], hr, gu[i]);  // K_x row ka = kc[ka] kr
-                gv[i] = fmaf(a.kr[ka], hc, gv[i]);  // K_y row ka = K_x column ka = kr[ka] kc
-            } else {
 #pragma unroll
-                for (int b = 0; b < N; ++b) {
-                    gu[i] = fmaf(a.kx[ka * N + b], d[b], gu[i]);
-                    gv[i] = fmaf(a.kx[b * N + ka], d[b], gv[i]);
+            for (int c = 0; c < CPT; ++c) {
+                if constexpr (SEP) {
+                    gu[i][c] = fmaf(kc[ka], hr[c], gu[i][c]);  // K_x row ka = kc[ka] kr
+                    gv[i][c] = fmaf(kr[ka], hc[c], gv[i][c]);  // K_y row ka = kr[ka] kc
+                } else {
+#pragma unroll
+                    for (int b = 0; b < N; ++b) {
+                        gu[i][c] = fmaf(a.kx[ka * N + b], d[b + c], gu[i][c]);
+                        gv[i][c] = fmaf(a.kx[b * N + ka], d[b + c], gv[i][c]);
+                    }
                 }
             }
         }
     }
 
+    // the sums are finished here: sunk to the pixel that uses them, they would
+    // keep every row's partial sums in registers
+    Mask ok[RPT][CPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i)
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            asm volatile("" : "+v"(gu[i][c]), "+v"(gv[i][c]));
+            ok[i][c] = mask_of(mn[i][c] > 0.f);
+        }
+
+    // pair reciprocals (lower or right minus upper or left) between the kept
+    // rows, the ones above pixel row i carried over from row i - 1
+    float pS[CPT], pSE[CPT + 1], pSW[CPT + 1];
+    auto vertical = [&](int u, float (&vS)[CPT], float (&vSE)[CPT + 1], float (&vSW)[CPT + 1]) {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) vS[c] = rcp(zk[u + 1][c + 1] - zk[u][c + 1]);
+#pragma unroll
+        for (int c = 0; c <= CPT; ++c) {
+            vSE[c] = rcp(zk[u + 1][c + 1] - zk[u][c]);
+            vSW[c] = rcp(zk[u + 1][c] - zk[u][c + 1]);
+        }
+    };
+    vertical(0, pS, pSE, pSW);
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
         const int y = y0 + top + i;
-        const int c = (top + i + R) * LW + lane + R;  // LDS index of the pixel
-        const float z0 = T[c].x;
-        float Gu, Gv;
-        if constexpr (KIND == KIND_DISP) {
-            Gu = fmaf(a.ksum, ref.y, gu[i]);
-            Gv = fmaf(a.ksum, ref.y, gv[i]);
-        } else {
-            Gu = ref.y * (gu[i] + a.ksum);
-            Gv = ref.y * (gv[i] + a.ksum);
-        }
-        const bool valid = mn[i] > 0.f;
-        // slots: E, W, S, N, SE, NW, SW, NE
-        const float zj[8] = {T[c + 1].x,      T[c - 1].x,      T[c + LW].x,     T[c - LW].x,
-                             T[c + LW + 1].x, T[c - LW - 1].x, T[c + LW - 1].x, T[c - LW + 1].x};
-        float rj[8];
+        float rE[CPT + 1], nS[CPT], nSE[CPT + 1], nSW[CPT + 1];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) rj[j] = rcp(zj[j] - z0);
-        const float fu = (float)x - f.u0, fv = (float)y - f.v0;
-        const float B = fmaf(fu, Gu, fv * Gv);
-        const float Spp = Gu + Gv, Spm = Gu - Gv;
-        const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};
-        bool general = true;
-        if constexpr (!kTieHeavy<KIND>) {
-            const float rmax = vmax8abs(rj[0], rj[1], rj[2], rj[3], rj[4], rj[5], rj[6], rj[7]);
-            general = __builtin_amdgcn_ballot_w64(valid && !(rmax < kInf)) != 0;
+        for (int c = 0; c <= CPT; ++c) rE[c] = rcp(zk[i + 1][c + 1] - zk[i + 1][c]);
+        vertical(i + 1, nS, nSE, nSW);
+        const float fv = (float)y - f.v0;
+        Vec<OT, CPT> ox, oy, oz;
+        bool mk[CPT];
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const float z0 = zk[i + 1][c + 1];
+            float Gu, Gv;
+            if constexpr (KIND == KIND_DISP) {
+                Gu = fmaf(a.ksum, ref.y, gu[i][c]);
+                Gv = fmaf(a.ksum, ref.y, gv[i][c]);
+            } else {
+                Gu = ref.y * (gu[i][c] + a.ksum);
+                Gv = ref.y * (gv[i][c] + a.ksum);
+            }
+            const Mask valid = ok[i][c];
+            // slots: E, W, S, N, SE, NW, SW, NE
+            const float zj[8] = {zk[i + 1][c + 2], zk[i + 1][c],     zk[i + 2][c + 1],
+                                 zk[i][c + 1],     zk[i + 2][c + 2], zk[i][c],
+                                 zk[i + 2][c],     zk[i][c + 2]};
+            const float rj[8] = {rE[c + 1],   -rE[c],  nS[c],  -pS[c],
+                                 nSE[c + 1], -pSE[c], nSW[c], -pSW[c + 1]};
+            const float fu = (float)(x + c) - f.u0;
+            const float B = fmaf(fu, Gu, fv * Gv);
+            bool general = true;
+            if constexpr (!kTieHeavy<KIND>) {
+                const float rmax = vmax8abs(rE[c + 1], rE[c], nS[c], pS[c], nSE[c + 1], pSE[c],
+                                            nSW[c], pSW[c + 1]);
+                general = (mask_of(rmax == kInf) & valid) != 0;
+            }
+            float nz;
+            if constexpr (AGG == AGG_MEAN) {
+                nz = mean8<KIND, false>(Gu, Gv, rj, zj, z0, B, general);
+            } else {
+                const float Spp = Gu + Gv, Spm = Gu - Gv;
+                const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};
+                nz = median8<KIND, false>(Nj, rj, zj, z0, B, general);
+            }
+            const float nx = f.fx * Gu, ny = f.fy * Gv;
+            const float n2 = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
+            const Mask pos = mask_of(n2 > 0.f);
+            const bool keep = ::sne::lane(valid & pos), deg = ::sne::lane(valid & ~pos);
+            const float rs = __builtin_amdgcn_rsqf(n2);
+            const float inv = keep ? rs : 0.f;
+            const float oz1 = mul_or_zero(nz, inv);
+            ox.v[c] = Out<OUT>::cvt(neg_mul_or_zero(nx, inv));
+            oy.v[c] = Out<OUT>::cvt(neg_mul_or_zero(ny, inv));
+            oz.v[c] = Out<OUT>::cvt(deg ? -1.f : oz1);
+            mk[c] = ::sne::lane(valid);
         }
-        const float nz = (AGG == AGG_MEAN) ? mean8<KIND, false>(Gu, Gv, rj, zj, z0, B, general)
-                                           : median8<KIND, false>(Nj, rj, zj, z0, B, general);
-        const float nx = f.fx * Gu, ny = f.fy * Gv;
-        const float n2 = fmaf(nx, nx, fmaf(ny, ny, nz * nz));
-        const bool deg = !(n2 > 0.f);
-        const float inv = __builtin_amdgcn_rsqf(n2);
-        const bool keep = valid && !deg;
-        const OT ox = Out<OUT>::cvt(keep ? -nx * inv : 0.f);
-        const OT oy = Out<OUT>::cvt(keep ? -ny * inv : 0.f);
-        const OT oz = Out<OUT>::cvt(keep ? nz * inv : (valid ? -1.f : 0.f));
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) pS[c] = nS[c];
+#pragma unroll
+        for (int c = 0; c <= CPT; ++c) {
+            pSE[c] = nSE[c];
+            pSW[c] = nSW[c];
+        }
         if (x < f.W && y < f.H) {
             SNE_GLOBAL char *o = store_base(f.out);
             const int64_t plane = f.out_plane * (int64_t)sizeof(OT);
             const unsigned off = ((unsigned)y * (unsigned)f.out_pitch + (unsigned)x) * sizeof(OT);
-            store_stream(o + off, ox);
-            store_stream(o + plane + off, oy);
-            store_stream(o + 2 * plane + off, oz);
-            if (f.mask)
-                store_stream(store_base(f.mask) +
-                                 ((unsigned)y * (unsigned)f.mask_pitch + (unsigned)x),
-                             (uint8_t)valid);
+            SNE_GLOBAL char *m =
+                store_base(f.mask) + ((unsigned)y * (unsigned)f.mask_pitch + (unsigned)x);
+            if (x + 1 < f.W) {
+                store_stream(o + off, ox);
+                store_stream(o + plane + off, oy);
+                store_stream(o + 2 * plane + off, oz);
+                if (f.mask) store_stream(m, (uint16_t)((mk[0] ? 1 : 0) | (mk[1] ? 0x100 : 0)));
+            } else {
+                store_stream(o + off, ox.v[0]);
+                store_stream(o + plane + off, oy.v[0]);
+                store_stream(o + 2 * plane + off, oz.v[0]);
+                if (f.mask) store_stream(m, (uint8_t)(mk[0] ? 1 : 0));
+            }
         }
     }
 }
@@ -1560,25 +1688,27 @@ hipError_t wide_r(const Variant &v, const WideArgs &a, hipStream_t s) {
     const dim3 grid((unsigned)a.nblocks), block(kBlock);
     if (v.agg == AGG_MEAN) {
         if (v.out == OUT_F32)
-            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEAN, OUT_F32, SEP>), grid, block, 0,
-                               s, a);
+            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEAN, OUT_F32, SEP>), grid,
+                               block, 0, s, a);
         else
-            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEAN, OUT_F16, SEP>), grid, block, 0,
-                               s, a);
+            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEAN, OUT_F16, SEP>), grid,
+                               block, 0, s, a);
     } else {
         if (v.out == OUT_F32)
-            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEDIAN, OUT_F32, SEP>), grid, block,
-                               0, s, a);
+            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEDIAN, OUT_F32, SEP>), grid,
+                               block, 0, s, a);
         else
-            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEDIAN, OUT_F16, SEP>), grid, block,
-                               0, s, a);
+            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEDIAN, OUT_F16, SEP>), grid,
+                               block, 0, s, a);
     }
     return hipGetLastError();
 }
 template <int KIND>
 hipError_t wide_variant(const Variant &v, const WideArgs &a, hipStream_t s) {
-    if (a.R == 2) return a.separable ? wide_r<KIND, 2, true>(v, a, s) : wide_r<KIND, 2, false>(v, a, s);
-    if (a.R == 3) return a.separable ? wide_r<KIND, 3, true>(v, a, s) : wide_r<KIND, 3, false>(v, a, s);
+    if (a.R == 2)
+        return a.separable ? wide_r<KIND, 2, true>(v, a, s) : wide_r<KIND, 2, false>(v, a, s);
+    if (a.R == 3)
+        return a.separable ? wide_r<KIND, 3, true>(v, a, s) : wide_r<KIND, 3, false>(v, a, s);
     return hipErrorInvalidValue;
 }
 template <int KIND>

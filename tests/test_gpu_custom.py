@@ -242,3 +242,55 @@ def test_wide_kernel_errors():
     n3, m3 = sne.estimate(raw, (30.0, 30.0, 14.5, 9.5), "depth_f32", "custom", "mean", ctx=ctx)
     torch.cuda.synchronize()
     assert int(m3.sum()) == 18 * 28
+
+
+@pytest.mark.parametrize("n", [5, 7])
+def test_wide_custom_kernels_any_width_and_alignment(n):
+    """Widths, heights, pitches and offsets around the 128 x 16 tile and its
+    two columns per thread, against the oracle; nothing outside the frame's own
+    elements is written, and frames of a batch equal single ones."""
+    rng = np.random.default_rng(8600 + n)
+    general = np.round(rng.uniform(-3, 3, size=(n, n))).astype(np.float32)
+    ctx = sne.Context(0, tuning=False)
+    r = n // 2
+    product = np.outer(np.arange(1, n + 1) % (r + 2) + 1.0, np.arange(-r, r + 1)).astype(np.float32)
+    for i, (H, W, pad, skew) in enumerate(((1, 1, 0, 0), (n, n, 0, 1), (15, 127, 1, 1),
+                                           (16, 128, 0, 0), (17, 129, 0, 1), (33, 131, 2, 3),
+                                           (9, 259, 1, 2))):
+        kx = product if i % 2 == 0 else general
+        ctx.set_gradient_kernel(kx)
+        K = (300.0, 300.0, (W - 1) / 2.0, (H - 1) / 2.0)
+        z = 2.0 + 0.001 * np.add.outer(np.arange(H), 0.7 * np.arange(W))
+        imgs = [(z + 1e-3 * rng.standard_normal((H, W))).astype(np.float32) for _ in range(2)]
+        imgs[1][rng.random((H, W)) < 0.01] = 0.0
+        pitch = W + pad
+        fs = H * pitch
+        store = torch.zeros(2 * fs + 8, device="cuda")
+        raw = store[skew:skew + 2 * fs].view(2, H, pitch)[:, :, :W]
+        for b in range(2):
+            raw[b].copy_(torch.from_numpy(imgs[b]))
+        for agg in ("mean", "median"):
+            for out in ("f32", "f16"):
+                dt = sne.OUT_DTYPE[sne.OUT[out]]
+                label = "wide %d %dx%d+%d/%d %s %s" % (n, H, W, pad, skew, agg, out)
+                say("case", label)
+                nbuf = torch.full((6 * fs + 16,), 7.0, dtype=dt, device="cuda")
+                mbuf = torch.full((2 * fs + 16,), 9, dtype=torch.uint8, device="cuda")
+                nv = nbuf[skew:skew + 6 * fs].view(2, 3, H, pitch)
+                mv = mbuf[skew:skew + 2 * fs].view(2, H, pitch)
+                sne.estimate_uniform(raw, K, "depth_f32", "custom", agg, out,
+                                     normals=nv[..., :W], mask=mv[..., :W], ctx=ctx)
+                torch.cuda.synchronize()
+                assert (nv[..., W:] == 7).all() and (mv[..., W:] == 9).all()
+                assert (nbuf[:skew] == 7).all() and (nbuf[skew + 6 * fs:] == 7).all()
+                assert (mbuf[:skew] == 9).all() and (mbuf[skew + 2 * fs:] == 9).all()
+                for b in range(2):
+                    on, om = oracle.estimate(imgs[b], "depth_f32", k32(K), kx.astype(np.float64), agg)
+                    gn, gm = nv[b, :, :, :W], mv[b, :, :W]
+                    check_parity(gn.double().cpu().numpy(), gm.cpu().numpy(), on, om, out, label)
+                    sn, sm = sne.estimate(raw[b], K, "depth_f32", "custom", agg, out, ctx=ctx)
+                    torch.cuda.synchronize()
+                    assert torch.equal(sm, gm), label
+                    assert torch.equal(sn.view(torch.int32 if out == "f32" else torch.int16),
+                                       gn.contiguous().view(torch.int32 if out == "f32"
+                                                            else torch.int16)), label
