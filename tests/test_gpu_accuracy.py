@@ -132,3 +132,30 @@ def test_accuracy_calls_on_two_streams():
     torch.cuda.synchronize()
     assert abs(r1[0].item() - t1.mean()) <= TOL_DEG and abs(r2[0].item() - t2.mean()) <= TOL_DEG
     assert int(r1[1].item()) == t1.size and r2[2].item() == 0.0
+
+
+@pytest.mark.parametrize("out", ["f32", "f16"])
+def test_accuracy_any_frame_size_and_alignment(out):
+    """Frames of fewer pixels than a group, frames whose last group is cut,
+    and buffers that start at any element, with up to 8 thresholds."""
+    rng = np.random.default_rng(31)
+    ctx = sne.Context(0)
+    phis = (5.0, 11.25, 22.5, 30.0, 60.0, 90.0, 120.0, 179.0)
+    for i, (B, h, w) in enumerate(((1, 1, 1), (700, 1, 3), (1, 1, 4), (333, 1, 5), (70, 2, 3),
+                                   (5, 1, 255), (3, 1, 257), (3000, 1, 7), (2, 33, 1031))):
+        skew, nphi = i % 4, (0, 1, 4, 5, 8)[i % 5]
+        shape = (B, h, w)
+        est, gt = _rotated(32 + i, shape, rng.uniform(0.0, 180.0, size=shape))
+        if out == "f16":
+            est = est.half()
+        mask = torch.from_numpy(rng.integers(0, 2, size=shape).astype(np.uint8)).cuda()
+
+        def moved(t, k):  # the same values, k elements into a buffer
+            buf = torch.zeros(t.numel() + 4, dtype=t.dtype, device="cuda")
+            v = buf[k:k + t.numel()].view(t.shape)
+            return v.copy_(t)
+
+        say("case", out, shape, skew, nphi)
+        _check(ctx, moved(est, skew), moved(gt, (skew + 1) % 4), moved(mask, (skew + 2) % 4),
+               phis[:nphi])
+        _check(ctx, est, gt, None, phis[:nphi])
