@@ -126,3 +126,22 @@ def test_any_width_and_alignment_bitwise(kind, out):
                 assert (n[..., W:] == 7).all() and (m[:, W:] == 9).all()
             for a, b in zip(ref, got):
                 assert torch.equal(a, b), (kind, out, W, pad, skew, px, rows, lanes)
+
+
+@pytest.mark.parametrize("agg", ["mean", "median"])
+@pytest.mark.parametrize("kind,scale,offset", [("depth_u16", 1, 0), ("depth_u16", 1, 65500),
+                                               ("depth_u16", 6000, 0), ("depth_f16", 2.0 ** -24, 0),
+                                               ("depth_f16", 2.0 ** -12, 0), ("depth_f16", 4096, 0)])
+def test_kept_candidates_at_the_ends_of_the_range(kind, scale, offset, agg):
+    """Neighbours that differ by the type's smallest step, near its smallest
+    and its largest values, and by most of its range: equal ones, and no
+    others, are left out."""
+    K = (60.0, 60.0, 40.5, 30.25)
+    small = _image("depth_u16", 9, 37, 131).astype(np.float64)
+    img = (small * scale + offset).astype(DTYPE[kind])
+    assert (img.astype(np.float64) == small * scale + offset).all()  # exact
+    for out in ("f32", "f16"):
+        n, m = sne.estimate(torch.from_numpy(img).cuda(), K, kind, "fd", agg, out)
+        on, om = oracle.estimate(img, ORACLE_KIND[kind], k32(K), "fd", agg)
+        check_parity(n.double().cpu().numpy(), m.cpu().numpy(), on, om, out,
+                     label="%s x %g + %g %s %s" % (kind, scale, offset, agg, out))
