@@ -145,3 +145,24 @@ def test_kept_candidates_at_the_ends_of_the_range(kind, scale, offset, agg):
         on, om = oracle.estimate(img, ORACLE_KIND[kind], k32(K), "fd", agg)
         check_parity(n.double().cpu().numpy(), m.cpu().numpy(), on, om, out,
                      label="%s x %g + %g %s %s" % (kind, scale, offset, agg, out))
+
+
+@pytest.mark.parametrize("kind", ["depth_f32", "disparity_f32"])
+def test_single_ties_at_every_column_fp32(kind):
+    """Single equal neighbours, in each of the 8 directions and at every column
+    of a tile, in an image without other ties."""
+    H, W, K = 57, 262, (60.0, 60.0, 130.5, 28.25)
+    rng = np.random.default_rng(9300)
+    scale = 2.0 if kind == "depth_f32" else 40.0
+    base = rng.permutation(H * W).reshape(H, W)  # all distinct
+    img = (scale * (1.0 + base / (H * W))).astype(np.float32)
+    dirs = [(dv, du) for dv in (-1, 0, 1) for du in (-1, 0, 1) if dv or du]
+    for v in range(2, H - 2, 4):
+        for u in range(1 + v % 5, W - 1, 5):
+            dv, du = dirs[(v // 4 + u) % 8]
+            img[v + dv, u + du] = img[v, u]
+    for out in ("f32", "f16"):
+        n, m = sne.estimate(torch.from_numpy(img).cuda(), K, kind, "fd", "mean", out)
+        on, om = oracle.estimate(img, ORACLE_KIND[kind], k32(K), "fd", "mean")
+        check_parity(n.double().cpu().numpy(), m.cpu().numpy(), on, om, out,
+                     label="%s %s" % (kind, out))
