@@ -1292,11 +1292,14 @@ __global__ __launch_bounds__(kBlock) SNE_OCCUPANCY void sne_uniform_kernel(Unifo
 // side, more than the three-row register window holds.  One block stages a
 // 128 x 16 output tile and its R-wide apron in LDS as (z, s) pairs (z = 0
 // where invalid or outside the frame), then each thread takes 2 columns by 4
-// rows of pixels.  The taps are formed against one reference sample of the
-// thread's pixels, inside the window of every one of them:
+// rows of pixels.  The taps are formed against one reference value z_r
+// (s_r = 1 / z_r), the mean of the four middle pixels, which lie in the
+// windows of all of them:
 // sum_ab K_ab s_ab = sum_ab K_ab (s_ab - s_r) + (sum K) s_r, with
 // s_ab - s_r = (z_r - z_ab) s_ab s_r from a raw-value difference (for
-// disparity d_ab - d_r), so each sample's difference serves all 8 pixels:
+// disparity d_ab - d_r), so each sample's difference serves all 8 pixels
+// (one pixel's sample as reference: 1.9e-7 rms of the 5x5 normals against 64
+// bits, the mean 1.2e-7):
 //   G = s_r (sum_ab K_ab (z_r - z_ab) s_ab + sum K)      (depth)
 //   G = sum_ab K_ab (d_ab - d_r) + (sum K) d_r            (disparity)
 // The neighbourhood of n_z stays the 8-connected one, and a pixel is kept iff
@@ -1330,7 +1333,7 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
     constexpr int CPT = kWideTW / kWave;           // columns per thread
     constexpr int S = N + CPT - 1;                 // samples of a window row
     static_assert(RPT * kWavesPerBlock == kWideTH && CPT == 2, "tile shape");
-    static_assert(RPT >= 2 && RPT - 2 <= R && CPT - 1 <= R, "the reference is in every window");
+    static_assert(RPT >= 3 && RPT - 2 <= R && CPT - 1 <= R, "the reference is in every window");
     static_assert(S % 2 == 0 && LW % 2 == 0, "16-byte LDS reads");
     __shared__ float4 T[LH * LW / 2];  // (z, s) of two columns
     using IT = typename Raw<KIND>::T;
@@ -1385,8 +1388,18 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
     const int top = wv * RPT;  // LDS row of pixel row 0's window top
     const int x = x0 + CPT * lane;
     const float4 *base = T + top * (LW / 2) + lane;  // the window's first pair
-    const float4 rf = base[(1 + R) * (LW / 2) + R / 2];
-    const float2 ref = R % 2 ? make_float2(rf.z, rf.w) : make_float2(rf.x, rf.y);
+    // the reference all window sums subtract: the mean of the four pixels in
+    // the middle of the thread's block, each in every window
+    float near[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float4 l = base[(1 + i + R) * (LW / 2) + R / 2];
+        near[i][0] = R % 2 ? l.z : l.x;
+        near[i][1] = R % 2 ? base[(1 + i + R) * (LW / 2) + R / 2 + 1].x : l.z;
+    }
+    const float rz = (0.25f * near[0][0] + 0.25f * near[0][1]) +
+                     (0.25f * near[1][0] + 0.25f * near[1][1]);
+    const float2 ref = make_float2(rz, KIND == KIND_DISP ? rz : rcp(rz));
     float kc[N], kr[N];
     if constexpr (SEP) {
 #pragma unroll
