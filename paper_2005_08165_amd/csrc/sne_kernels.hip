@@ -11,9 +11,10 @@
 // Horizontal neighbours that live in the adjacent lane arrive by DPP wave
 // shifts; the two columns just outside a tile are loaded by its first and
 // last lanes and enter through the DPP "old" operand.
-// No LDS and no barriers are involved, so a tile's arithmetic is the same
-// instruction sequence whatever the launch shape: results are bitwise
-// identical alone, in a uniform batch and in an uneven persistent batch.
+// No barriers are involved (and LDS only to turn packed output rows around
+// within a wavefront), so a tile's arithmetic is the same instruction sequence
+// whatever the launch shape: results are bitwise identical alone, in a uniform
+// batch and in an uneven persistent batch.
 //
 // Arithmetic (FP32), per pixel p with raw value z (depth) or d (disparity):
 //   s = 1/z (depth) or d (disparity): the image the gradient filters see
