@@ -263,7 +263,7 @@ int sne_get_tile(sne_ctx *ctx, int32_t H, int32_t W, int32_t B, int kind, int gr
  * others.  Unaligned rows make the cache lines at the edges of every strip of
  * columns shared between wavefronts, which costs HBM bandwidth and favours
  * short tiles; 128 x 375x1242 FP32 disparity frames, Scharr-median, run in
- * 212 us dense (pitch 1242) and in 197 us at pitch 1280 on an MI355X.
+ * 212 us dense (pitch 1242) and in 194 us at pitch 1280 on an MI355X.
  * sne_row_pitch returns the smallest pitch (elements) >= W whose rows are
  * 256-byte multiples, for elements of elem_bytes = 1, 2 or 4 bytes;
  * SNE_ERR_ARG for W < 1 or another element size. */
