@@ -116,60 +116,110 @@ int max_px(const void *in, const void *out, int W, int kind, int out_type) {
 
 int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 
-// Tile shape when nothing is cached, fitted to sweeps over 20 workloads (one
-// frame to 100, widths 400 to 3840, every input kind; the choice is within
-// 10 % of the best shape of each but for a few small batches).
+// Tile shape when nothing is cached, fitted to sweeps of every shape over 400
+// workloads (one frame of 101x103 to 64 of 480x640, every input kind, both
+// rules, several sets of buffers in turn).
 //
-// Columns per lane and half waves: the least work per row of the frame.  A
-// lane's row costs about 40 + 60 px instructions whatever its columns hold;
-// half waves cost 5 % more, and 30 % where rows do not start at multiples of
-// their 4-column vectors (20 x 1001x1333 FP32 Scharr-median: 133 us in half
-// waves, 98 in full ones).  The lenient rule's kernels hold so many registers
-// at 4 columns that 2 are faster (64 x 480x640: 87 against 101 us).
+// Small launches, up to about one round of wavefronts: a call's time is that of
+// one wavefront, which walks its rows one after the other, so the work goes to
+// as many wavefronts as help.  FP32 input: 1 column and 1 or 2 rows while they
+// make no more than 8 wavefronts per CU, then 2 columns, or 4 where FP16 output
+// makes their stores 8 bytes and no lanes are wasted.  16-bit input, bound by
+// instruction issue: 1 column throughout.  One frame's kernel, against half
+// waves or 4 columns by 4 rows: 101x103 FP32 FD-mean 3.0 us (5.0), 240x320
+// Sobel-median 3.0 (5.3), 480x640 FD-mean 3.8 (6.0), u16 FD-median 4.1 (6.8),
+// 375x1242 Sobel-median 4.7 (8.0); 4 frames of 480x640 6.7 (8.4), 8 of them 9.8
+// (10.7).  The shape is 2 % slower than the best of such a workload on average,
+// 17 % at most.
+//
+// Larger ones, columns per lane and half waves: the least work per row of the
+// frame.  A lane's row costs about 40 + 60 px instructions whatever its columns
+// hold; half waves cost 5 % more, and at widths that are no multiple of their
+// 4-column vectors 30 % with FP32 output (20 x 1001x1333 Scharr-median: 133 us
+// in half waves, 98 in full ones) and 10 % with FP16.  The lenient rule's
+// kernels hold so many registers at 4 columns that 2 are faster (64 x 480x640
+// Sobel-median: 87 against 101 us).
 //
 // Rows: 8 where there are enough tiles for it, 4 otherwise (the first row of
-// a tile costs about two); FP32 rows of a width that is no multiple of 256 bytes
-// share a cache line between the wavefronts of neighbouring strips, which
-// should write it at about the same time: 4, or 2 in large batches (40 x
-// 500x1242 disparity Sobel-mean: 2 rows 84-91 us, 4 rows 102, 8 rows 109;
-// with padded rows, Scharr-median, 70, 73 and 84 us).
+// a tile costs about two); FP32 output of a width that is no multiple of 256
+// bytes, at any pitch: 4, or 2 in large batches of FP32 input.  With dense rows
+// neighbouring strips share a cache line, which their wavefronts should write at
+// about the same time (40 x 500x1242 disparity Sobel-median: 2 rows 91 us, 4
+// rows 102, 8 rows 109).  Padded rows have no such lines and no height that is
+// best for all (same batch, FP32 depth: FD-mean 2 rows 67 us, 4 rows 76, 8 rows
+// 82; Sobel-median 83, 75, 81).  16-bit input wants the taller tile (20 x
+// 1001x1333 u16 Sobel-median, padded: 2 rows 108 us, 4 rows 99).  The shape is
+// 5 % slower than the best of such a workload on average, 28 % at most.
 // Uneven batches: 20 rows (the persistent kernel finds a frame per tile) if
 // that leaves enough tiles.
 //
-// Blocks go out in runs of kChunkOrder per XCD, which is the best or within
-// 3 % of it everywhere.
+// Block order: one range of tiles per XCD while input and output stay in the
+// last-level cache (the halo rows of neighbouring tiles then meet in that XCD's
+// L2: 5 % less time than runs of kChunkOrder from 427x561 on), runs of
+// kChunkOrder for batches that stream from HBM.
 TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, const Variant &v,
                         bool uneven) {
     // packed pixels: 16 bytes each, so 2 columns and 4 rows have as much to
     // store as 4 and 8 of the planes (64 x 480x640 FP32 Sobel-median: 2 x 4
     // rows 89 us, 4 x 4 94, 1 x 8 96; 70 x 238x494 FP16 Sobel-mean: 34, 37, 36)
     if (v.out == OUT_RGBN) return TileChoice{std::min(pxmax, 2), 4, kChunkOrder, 0};
-    TileChoice best{1, 4, kChunkOrder, 0};
-    double best_cost = 0.0;
+    const int64_t cu = ctx ? ctx->num_cu : 256;
+    const auto lanes = [&](int px, int half) {  // what a row of the frame takes
+        const TileChoice t{px, 1, kChunkOrder, half};
+        return (double)tile_nstrips(W, t) * (half ? 32 : 64) *
+               (!half ? 1.0 : W % 4 == 0 ? 1.05 : v.out == SNE_OUT_F32 ? 1.3 : 1.1);
+    };
+    const auto waves = [&](const TileChoice &t) {  // of tiles of 1 row
+        return B * H * tile_nstrips(W, t) / (t.half ? 2 : 1);
+    };
+    const auto half_of = [&](int px) { return lanes(px, 1) < lanes(px, 0) ? 1 : 0; };
+    const auto work = [&](int px, int half) { return lanes(px, half) * (40 + 60 * px); };
     const int widest = (v.kind & SNE_LENIENT) ? std::min(pxmax, 2) : pxmax;
+    if (!uneven) {
+        const bool four = v.out == SNE_OUT_F16 && widest == 4 &&
+                          work(4, half_of(4)) < work(2, half_of(2));
+        // at most `rows` rows, fewer while that makes no more than `aim`
+        // wavefronts per CU; not for launches of more than `most` per CU
+        struct Step {
+            int px, rows, aim, most;
+        };
+        const Step fp32[] = {{1, 2, 8, 8}, {2, 2, 10, 10}, {four ? 4 : 2, 4, 20, 20}};
+        const Step quantised[] = {{1, 5, 8, (v.kind & SNE_LENIENT) ? 60 : 40}};
+        const bool q = in_elem(v.kind) == 2;
+        for (const Step *s = q ? quantised : fp32; s != (q ? quantised + 1 : fp32 + 3); ++s) {
+            if (s->px > pxmax) continue;
+            TileChoice t{s->px, s->rows, 1, half_of(s->px)};
+            const int64_t w = waves(t);
+            if (w > cu * s->most * s->rows) continue;
+            t.rows = (int)std::min<int64_t>(s->rows, std::max<int64_t>(
+                                                         1, (w + cu * s->aim - 1) / (cu * s->aim)));
+            return t;
+        }
+    }
+    const int64_t bytes = B * H * W * (int64_t)(in_elem(v.kind) + 3 * out_elem(v.out) + 1);
+    const int order = bytes <= (128 << 20) ? 1 : kChunkOrder;
+    TileChoice best{1, 4, order, 0};
+    double best_cost = 0.0;
     for (int px : {4, 2, 1}) {
         if (px > widest) continue;
         for (int half : {0, 1}) {
-            const TileChoice t{px, 4, kChunkOrder, half};
-            const double lanes = (double)tile_nstrips(W, t) * (half ? 32 : 64);
-            const double cost = lanes * (40 + 60 * px) * (!half ? 1.0 : W % 4 ? 1.3 : 1.05);
+            const double cost = work(px, half);
             if (best_cost == 0.0 || cost < best_cost) {
-                best = t;
+                best = TileChoice{px, 4, order, half};
                 best_cost = cost;
             }
         }
     }
-    // tiles of 1 row, in wavefronts; 4 per SIMD are resident
-    const int64_t waves = B * H * tile_nstrips(W, best) / (best.half ? 2 : 1);
-    const int64_t full = (int64_t)(ctx ? ctx->num_cu : 256) * 16;
+    const int64_t full = cu * 16;  // wavefronts, 4 per SIMD, are resident
     if (uneven) {
-        best.rows = (int)std::min<int64_t>(std::max<int64_t>(waves / full, 2), 20);
+        best.rows = (int)std::min<int64_t>(std::max<int64_t>(waves(best) / full, 2), 20);
         return best;
     }
     best.rows = 8;
-    if (v.out == SNE_OUT_F32 && W * 4 % kRowAlign != 0)
-        best.rows = !(v.kind & SNE_LENIENT) && B * H * W > (16 << 20) ? 2 : 4;
-    if (best.rows == 8 && waves / 8 < full * 9 / 10) best.rows = 4;
+    if (v.out == SNE_OUT_F32 && (int64_t)W * 4 % kRowAlign != 0)
+        best.rows = !(v.kind & SNE_LENIENT) && in_elem(v.kind) == 4 && B * H * W > (16 << 20)
+                        ? 2 : 4;
+    if (best.rows == 8 && waves(best) / 8 < full * 9 / 10) best.rows = 4;
     return best;
 }
 

@@ -262,3 +262,21 @@ def test_rgbn_argument_errors():
                 dict(B=2, out_fs=63)]:
         a = dict(good, **bad)
         assert L.sne_estimate_rgbn(*a.values()) == sne.SNE_ERR_ARG, bad
+
+
+@pytest.mark.parametrize("B,H,W", [(1, 101, 103), (1, 240, 320), (1, 375, 1242), (1, 427, 561),
+                                   (1, 480, 640), (1, 720, 1280), (4, 480, 640), (8, 480, 640),
+                                   (1, 1080, 1920)])
+@pytest.mark.parametrize("kind", ["depth_f32", "depth_u16", "disparity_f32", "depth_f32+lenient"])
+def test_default_tile_spreads_small_launches(B, H, W, kind):
+    """A launch that does not fill the GPU (256 CUs, 4 SIMDs each) takes as long
+    as one of its wavefronts, which walks its rows one after the other: without
+    a tuned entry it makes at least one wavefront per SIMD, or one per 64
+    pixels of a row where the image has no more."""
+    t = sne.Tile()
+    assert sne.lib().sne_get_tile(None, H, W, B, sne._kind(kind), sne.GRAD["fd"],
+                                  sne.AGG["mean"], sne.OUT["f32"], ctypes.byref(t)) == 0
+    strips = -(-W // (t.lanes * t.cols_per_lane))
+    bands = -(-H // t.rows)
+    waves = B * strips * (-(-bands // 2) if t.lanes == 32 else bands)
+    assert waves >= min(1024, B * H * -(-W // 64)), (t.cols_per_lane, t.rows, t.lanes, waves)
