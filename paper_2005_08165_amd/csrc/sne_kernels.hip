@@ -91,9 +91,6 @@ constexpr float kInf = __builtin_huge_valf();
 // +denormal | +normal, i.e. 0 < x <= FLT_MAX
 constexpr int kPosFinite = (1 << 7) | (1 << 8);
 
-// NaN, -infinity or +infinity
-constexpr int kNonFinite = (1 << 0) | (1 << 1) | (1 << 2) | (1 << 9);
-
 // lane l receives lane l-1's `src`; lane 0 (no source) keeps `old`.
 __device__ __forceinline__ float from_left(float old, float src) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
@@ -437,15 +434,6 @@ __device__ __forceinline__ float pair_or_zero(float a, float b, Mask oka, Mask o
 // -> 46.8 us, binary16 50.5 -> 47.6 us; 1024 uneven u16 frames 1.78 -> 1.74 ms.
 template <int KIND, int AGG, bool LEN>
 constexpr bool kPairCount = kPairMean<KIND, AGG, LEN> && kTieHeavy<KIND> && !LEN;
-
-// Of the others, strict means of FP32 values look at the plain sum for a
-// left-out slot instead of at the eight reciprocals (tile_row): one half-rate
-// instruction per pixel instead of five.  64 x 480x640 Sobel-mean FP16 output
-// 45.3 -> 43.2 us, 200 uneven FP32 frames FD-mean FP16 387 -> 366 us.  One
-// vote and branch per row instead of per pixel held more registers and was
-// 1-3 % slower.
-template <int KIND, int AGG, bool LEN>
-constexpr bool kMeanVote = AGG == AGG_MEAN && !kPairMean<KIND, AGG, LEN>;
 
 template <int KIND>
 __device__ __forceinline__ float pair_counted(float a, float b, float &count) {
@@ -1008,18 +996,11 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
             // this wavefront needs it (the choice is wave-uniform, and both paths
             // give the same result when nothing is left out).
             // (signs do not matter here: the raw pair values are used)
-            if constexpr (kMeanVote<KIND, AGG, LEN>) {
-                // a left-out slot's infinite reciprocal makes the plain sum
-                // infinite or NaN (valid samples are positive, so nothing
-                // cancels it): one class test of the result says the same
-                float unused;
-                nz[k] = normal_z<KIND, AGG, LEN, false, PX>(k, f, col, fv, Gu[k], Gv[k], unused,
-                                                            rp, rc, rn, pu, pd);
-                if ((mask_of(__builtin_amdgcn_classf(nz[k], kNonFinite)) & valid[k]) != 0)
-                    nz[k] = normal_z<KIND, AGG, LEN, true, PX>(k, f, col, fv, Gu[k], Gv[k], unused,
-                                                               rp, rc, rn, pu, pd);
-                continue;
-            }
+            // For the mean, a class test of the plain sum says the same in one
+            // half-rate instruction instead of five, but a pixel with ties
+            // then forms both sums: 64 x 480x640 FD-mean, FP16 output, 42.6
+            // instead of 42.9 us on depth without ties, 57.0 instead of 51.1
+            // on millimetres converted to metres.
             if constexpr (!kTieHeavy<KIND> && !kPairMean<KIND, AGG, LEN>) {
                 const int c = k + 1;
                 const float rmax = vmax8abs(rc.rE[c], rc.rE[c - 1], pd.rS[k], pu.rS[k], pd.rSE[c],
