@@ -153,10 +153,12 @@ int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 // Uneven batches: 20 rows (the persistent kernel finds a frame per tile) if
 // that leaves enough tiles.
 //
-// Block order: one range of tiles per XCD while input and output stay in the
-// last-level cache (the halo rows of neighbouring tiles then meet in that XCD's
-// L2: 5 % less time than runs of kChunkOrder from 427x561 on), runs of
-// kChunkOrder for batches that stream from HBM.
+// Block order: one range of tiles per XCD for small launches (the halo rows of
+// neighbouring tiles then meet in that XCD's L2: 5 % less time than runs of
+// kChunkOrder from 427x561 on) and, bound by issue, for larger ones that stay in
+// the last-level cache (2 x 1080x1920 u16 2-6 %); runs of kChunkOrder where HBM
+// is the limit or strips share lines (16 x 375x1242 u16 Sobel-median 12 % less
+// time than one range, lenient FD-mean 16 %).
 TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, const Variant &v,
                         bool uneven) {
     // packed pixels: 16 bytes each, so 2 columns and 4 rows have as much to
@@ -196,8 +198,13 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
             return t;
         }
     }
+    // output rows of a width that is no multiple of 256 bytes, at any pitch
+    const bool cut = (int64_t)W * (int64_t)out_elem(v.out) % kRowAlign != 0;
+    const bool f32 = v.out == SNE_OUT_F32;
+    const bool light = in_elem(v.kind) == 4 && !(v.kind & SNE_LENIENT);
     const int64_t bytes = B * H * W * (int64_t)(in_elem(v.kind) + 3 * out_elem(v.out) + 1);
-    const int order = bytes <= (128 << 20) ? 1 : kChunkOrder;
+    const bool one_range = bytes <= (128 << 20) && !(cut && f32) && !(light && (cut || f32));
+    const int order = one_range ? 1 : kChunkOrder;
     TileChoice best{1, 4, order, 0};
     double best_cost = 0.0;
     for (int px : {4, 2, 1}) {
@@ -216,9 +223,7 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
         return best;
     }
     best.rows = 8;
-    if (v.out == SNE_OUT_F32 && (int64_t)W * 4 % kRowAlign != 0)
-        best.rows = !(v.kind & SNE_LENIENT) && in_elem(v.kind) == 4 && B * H * W > (16 << 20)
-                        ? 2 : 4;
+    if (cut && f32) best.rows = light && B * H * W > (16 << 20) ? 2 : 4;
     if (best.rows == 8 && waves(best) / 8 < full * 9 / 10) best.rows = 4;
     return best;
 }
