@@ -61,8 +61,9 @@ struct UniformArgs {
 };
 
 // Wide custom gradient filters: a (2R+1)x(2R+1) K_x (R = 2, 3; K_y = K_x^T)
-// over a uniform batch, one block per 128 x 16 output tile of a frame.
-constexpr int kWideTW = 128, kWideTH = 16;  // output tile; 2 x 4 pixels per thread
+// over a uniform batch, one block per (64 cols) x 16 output tile of a frame,
+// cols x 4 pixels per thread.
+constexpr int kWideTH = 16;
 constexpr int kWideMaxN = 7;
 struct WideArgs {
     FrameDesc f;
@@ -70,6 +71,7 @@ struct WideArgs {
     int32_t ntx, nty;                               // tiles per frame, x and y
     int32_t nblocks;                                // B * ntx * nty
     int32_t R;                                      // 2 or 3
+    int32_t cols;                                   // columns per thread, 1 or 2
     float kx[kWideMaxN * kWideMaxN];                // K_x row-major, (2R+1)^2 used
     float ksum;                                     // sum of all weights
     int32_t separable;                              // 1: K_x[a][b] = kc[a] kr[b]

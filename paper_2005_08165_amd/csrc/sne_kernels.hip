@@ -1272,8 +1272,8 @@ __global__ __launch_bounds__(kBlock) SNE_OCCUPANCY void sne_uniform_kernel(Unifo
 // ------------------------------------------------ wide custom gradient filters
 // A (2R+1)x(2R+1) custom K_x (R = 2, 3; K_y = K_x^T) reads R samples on each
 // side, more than the three-row register window holds.  One block stages a
-// 128 x 16 output tile and its R-wide apron in LDS as (z, s) pairs (z = 0
-// where invalid or outside the frame), then each thread takes 2 columns by 4
+// 128 x 16 (64 x 16) output tile and its R-wide apron in LDS as (z, s) pairs (z = 0
+// where invalid or outside the frame), then each thread takes 2 columns (1) by 4
 // rows of pixels.  The taps are formed against one reference value z_r
 // (s_r = 1 / z_r), the mean of the four middle pixels, which lie in the
 // windows of all of them:
@@ -1291,12 +1291,15 @@ __global__ __launch_bounds__(kBlock) SNE_OCCUPANCY void sne_uniform_kernel(Unifo
 // pixel takes 2(2R+1) FMAs of row sums instead of 2(2R+1)^2 taps.  Its weights
 // are held in vector registers: an FMA with a scalar operand issues at half
 // rate.
-// Bound by instruction issue.  Two columns per thread share the reference's
-// differences, the row minima and the pairs between them (6 instead of 8
-// reciprocals per pixel): 64 x 480x640 FP32 median, 5x5 product 73 us (98
-// with one column), 7x7 product 87 (128 before the series), 5x5 general 79
-// (117).  Tiles of 8 rows, 2 per thread, were no faster where 16-row tiles leave
-// CUs idle (one 480x640 frame 8.6 us with either; 8 frames 13.6 against 12.3).
+// Bound by instruction issue.  Two columns per thread (CPT) share the
+// reference's differences, the row minima and the pairs between them (6 instead
+// of 8 reciprocals per pixel): 64 x 480x640 FP32 median, 5x5 product 73 us (98
+// with one column), 7x7 product 87 (128), 5x5 general 79 (117).  A launch of
+// few blocks takes as long as one thread: there one column per thread, half the
+// tile, with the reference of the pair of columns, so that the bits stay the
+// same (one frame, 5x5 product, FP32 median: 240x320 4.6 us, 6.1 with two
+// columns, 480x640 5.5 against 6.4).  Tiles of 8 rows, 2 per thread, were no
+// faster there (480x640 8.6 us with either at two columns).
 // Blocks run in runs of kWideRun per XCD (xcd_chunk), so the tiles above and
 // below a tile mostly share its apron rows through one L2.
 constexpr int kWideRun = 16;
@@ -1308,15 +1311,15 @@ __device__ __forceinline__ float in_vgpr(float x) {
     return r;
 }
 
-template <int KIND, int R, int AGG, int OUT, bool SEP>
+template <int KIND, int R, int AGG, int OUT, bool SEP, int CPT>
 __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
-    constexpr int N = 2 * R + 1, LW = kWideTW + 2 * R, LH = kWideTH + 2 * R;
+    constexpr int TW = kWave * CPT;                // tile width
+    constexpr int N = 2 * R + 1, LW = TW + 2 * R, LH = kWideTH + 2 * R;
     constexpr int RPT = kWideTH / kWavesPerBlock;  // rows per thread
-    constexpr int CPT = kWideTW / kWave;           // columns per thread
     constexpr int S = N + CPT - 1;                 // samples of a window row
-    static_assert(RPT * kWavesPerBlock == kWideTH && CPT == 2, "tile shape");
-    static_assert(RPT >= 3 && RPT - 2 <= R && CPT - 1 <= R, "the reference is in every window");
-    static_assert(S % 2 == 0 && LW % 2 == 0, "16-byte LDS reads");
+    static_assert(RPT * kWavesPerBlock == kWideTH && (CPT == 1 || CPT == 2), "tile shape");
+    static_assert(RPT >= 3 && RPT - 2 <= R && R >= 1, "the reference is in every window");
+    static_assert((CPT == 1 || S % 2 == 0) && LW % 2 == 0, "16-byte LDS reads");
     __shared__ float4 T[LH * LW / 2];  // (z, s) of two columns
     using IT = typename Raw<KIND>::T;
     using OT = typename Out<OUT>::T;
@@ -1326,7 +1329,7 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
     const int frame = blk / per_frame;
     const int rem = blk - frame * per_frame;
     const int ty = rem / a.ntx;
-    const int x0 = (rem - ty * a.ntx) * kWideTW, y0 = ty * kWideTH;
+    const int x0 = (rem - ty * a.ntx) * TW, y0 = ty * kWideTH;
     FrameDesc f = a.f;
     f.in = static_cast<const IT *>(a.f.in) + frame * a.in_fstride;
     f.out = static_cast<OT *>(a.f.out) + frame * a.out_fstride;
@@ -1337,10 +1340,11 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
     // stage pairs of columns (gx, gx + 1); samples outside the frame read as 0
-    // (invalid).  Wavefront wv takes rows wv, wv + 4, ... of the first 64
-    // pairs, and the apron pairs right of them go one to a thread; all loads
-    // are issued before the first is used.
-    constexpr int kPasses = (LH + kWavesPerBlock - 1) / kWavesPerBlock;
+    // (invalid).  A wavefront takes the first TW / 2 pairs of one row (of two
+    // with CPT 1) at a time, and the apron pairs right of them go one to a
+    // thread; all loads are issued before the first is used.
+    constexpr int kPairs = TW / 2, kRows = kBlock / kPairs;  // rows per pass
+    constexpr int kPasses = (LH + kRows - 1) / kRows;
     static_assert(LH * R <= kBlock, "one apron pair per thread");
     IT z0[kPasses + 1], z1[kPasses + 1];
     auto load_pair = [&](int row, int pair, IT &l, IT &r) {
@@ -1355,23 +1359,26 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
         T[row * (LW / 2) + pair] = make_float4(zl, KIND == KIND_DISP ? zl : rcp(zl), zr,
                                                KIND == KIND_DISP ? zr : rcp(zr));
     };
-    const int arow = (int)threadIdx.x / R, apair = kWave + (int)threadIdx.x % R;
+    const int row0 = CPT == 2 ? wv : (int)threadIdx.x / kPairs;
+    const int pair0 = (int)threadIdx.x & (kPairs - 1);
+    const int arow = (int)threadIdx.x / R, apair = kPairs + (int)threadIdx.x % R;
     const bool apron = (int)threadIdx.x < LH * R;
 #pragma unroll
-    for (int i = 0; i < kPasses; ++i) load_pair(wv + i * kWavesPerBlock, lane, z0[i], z1[i]);
+    for (int i = 0; i < kPasses; ++i) load_pair(row0 + i * kRows, pair0, z0[i], z1[i]);
     if (apron) load_pair(arow, apair, z0[kPasses], z1[kPasses]);
 #pragma unroll
     for (int i = 0; i < kPasses; ++i)
-        if (LH % kWavesPerBlock == 0 || wv + i * kWavesPerBlock < LH)
-            put_pair(wv + i * kWavesPerBlock, lane, z0[i], z1[i]);
+        if (LH % kRows == 0 || row0 + i * kRows < LH)
+            put_pair(row0 + i * kRows, pair0, z0[i], z1[i]);
     if (apron) put_pair(arow, apair, z0[kPasses], z1[kPasses]);
     __syncthreads();
 
     const int top = wv * RPT;  // LDS row of pixel row 0's window top
     const int x = x0 + CPT * lane;
-    const float4 *base = T + top * (LW / 2) + lane;  // the window's first pair
+    // the first pair of the window; of that of the even column with CPT 1
+    const float4 *base = T + top * (LW / 2) + lane / (2 / CPT);
     // the reference all window sums subtract: the mean of the four pixels in
-    // the middle of the thread's block, each in every window
+    // the middle of 2 columns by 4 rows, each in the windows of all of these
     float near[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -1408,25 +1415,37 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
         // first and takes 136 registers
         __builtin_amdgcn_sched_barrier(0);
         float zv[S], d[S];
+        const auto diff = [&](float z, float sv) {
+            return KIND == KIND_DISP ? sv - ref.y : (ref.x - z) * sv;
+        };
+        if constexpr (CPT == 2) {
 #pragma unroll
-        for (int b = 0; b < S; b += 2) {
-            const float4 t = base[ar * (LW / 2) + b / 2];
-            zv[b] = t.x;
-            zv[b + 1] = t.z;
-            d[b] = KIND == KIND_DISP ? t.y - ref.y : (ref.x - t.x) * t.y;
-            d[b + 1] = KIND == KIND_DISP ? t.w - ref.y : (ref.x - t.z) * t.w;
+            for (int b = 0; b < S; b += 2) {
+                const float4 t = base[ar * (LW / 2) + b / 2];
+                zv[b] = t.x;
+                zv[b + 1] = t.z;
+                d[b] = diff(t.x, t.y);
+                d[b + 1] = diff(t.z, t.w);
+            }
+        } else {
+            const float2 *line = reinterpret_cast<const float2 *>(T) + (top + ar) * LW + lane;
+#pragma unroll
+            for (int b = 0; b < S; ++b) {
+                zv[b] = line[b].x;
+                d[b] = diff(line[b].x, line[b].y);
+            }
         }
         if (ar >= R - 1 && ar <= R + RPT) {
 #pragma unroll
             for (int c = 0; c < CPT + 2; ++c) zk[ar - (R - 1)][c] = zv[R - 1 + c];
         }
-        // minima of the row's two windows: zv[1..2R] is common
+        // minima of the row's windows: zv[1..2R] is common to two
         float both = vmin3(zv[1], zv[2], zv[3]);
 #pragma unroll
         for (int b = 4; b + 1 <= 2 * R; b += 2)
             if (b + 1 < 2 * R) both = vmin3(both, zv[b], zv[b + 1]);
         rmin[ar & 1][0] = vmin3(both, zv[0], zv[2 * R]);
-        rmin[ar & 1][1] = vmin3(both, zv[2 * R], zv[2 * R + 1]);
+        if constexpr (CPT == 2) rmin[ar & 1][1] = vmin3(both, zv[2 * R], zv[2 * R + 1]);
         if (ar & 1) {  // two rows at a time into the windows that hold them
 #pragma unroll
             for (int i = 0; i < RPT; ++i)
@@ -1565,11 +1584,12 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
             const unsigned off = ((unsigned)y * (unsigned)f.out_pitch + (unsigned)x) * sizeof(OT);
             SNE_GLOBAL char *m =
                 store_base(f.mask) + ((unsigned)y * (unsigned)f.mask_pitch + (unsigned)x);
-            if (x + 1 < f.W) {
+            if (CPT == 2 && x + 1 < f.W) {
                 store_stream(o + off, ox);
                 store_stream(o + plane + off, oy);
                 store_stream(o + 2 * plane + off, oz);
-                if (f.mask) store_stream(m, (uint16_t)((mk[0] ? 1 : 0) | (mk[1] ? 0x100 : 0)));
+                if (f.mask)
+                    store_stream(m, (uint16_t)((mk[0] ? 1 : 0) | (mk[CPT - 1] ? 0x100 : 0)));
             } else {
                 store_stream(o + off, ox.v[0]);
                 store_stream(o + plane + off, oy.v[0]);
@@ -1757,25 +1777,29 @@ hipError_t uniform_variant(const Variant &v, const UniformArgs &a, int grid, hip
     }
     return SNE_DISPATCH(uniform_px, KIND, v, a, grid, s);
 }
-template <int KIND, int R, bool SEP>
-hipError_t wide_r(const Variant &v, const WideArgs &a, hipStream_t s) {
+template <int KIND, int R, bool SEP, int CPT>
+hipError_t wide_cols(const Variant &v, const WideArgs &a, hipStream_t s) {
     const dim3 grid((unsigned)a.nblocks), block(kBlock);
     if (v.agg == AGG_MEAN) {
         if (v.out == OUT_F32)
-            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEAN, OUT_F32, SEP>), grid,
+            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEAN, OUT_F32, SEP, CPT>), grid,
                                block, 0, s, a);
         else
-            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEAN, OUT_F16, SEP>), grid,
+            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEAN, OUT_F16, SEP, CPT>), grid,
                                block, 0, s, a);
     } else {
         if (v.out == OUT_F32)
-            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEDIAN, OUT_F32, SEP>), grid,
+            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEDIAN, OUT_F32, SEP, CPT>), grid,
                                block, 0, s, a);
         else
-            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEDIAN, OUT_F16, SEP>), grid,
+            hipLaunchKernelGGL((sne_wide_kernel<KIND, R, AGG_MEDIAN, OUT_F16, SEP, CPT>), grid,
                                block, 0, s, a);
     }
     return hipGetLastError();
+}
+template <int KIND, int R, bool SEP>
+hipError_t wide_r(const Variant &v, const WideArgs &a, hipStream_t s) {
+    return a.cols == 1 ? wide_cols<KIND, R, SEP, 1>(v, a, s) : wide_cols<KIND, R, SEP, 2>(v, a, s);
 }
 template <int KIND>
 hipError_t wide_variant(const Variant &v, const WideArgs &a, hipStream_t s) {

@@ -294,3 +294,59 @@ def test_wide_custom_kernels_any_width_and_alignment(n):
                     assert torch.equal(sn.view(torch.int32 if out == "f32" else torch.int16),
                                        gn.contiguous().view(torch.int32 if out == "f32"
                                                             else torch.int16)), label
+
+
+@pytest.mark.parametrize("kind", ["depth_f32", "depth_u16", "disparity_f32"])
+@pytest.mark.parametrize("n", [5, 7])
+def test_wide_custom_batches_equal_single_frames_bitwise(n, kind):
+    """Large batches give each thread two columns, small ones one: the same
+    bits, at widths and heights around both tiles (128 x 16 and 64 x 16), and
+    nothing outside the frames' own elements is written."""
+    rng = np.random.default_rng(8700 + n)
+    ctx = sne.Context(0, tuning=False)
+    r = n // 2
+    product = np.outer(np.arange(1, n + 1) % (r + 2) + 1.0, np.arange(-r, r + 1)).astype(np.float32)
+    general = np.round(rng.uniform(-3, 3, size=(n, n))).astype(np.float32)
+    for i, (H, W, pad, skew) in enumerate(((1, 1, 0, 0), (n, n, 0, 1), (15, 63, 1, 1),
+                                           (16, 128, 0, 0), (17, 129, 0, 1), (33, 131, 2, 3),
+                                           (9, 259, 1, 2), (31, 65, 0, 0))):
+        ctx.set_gradient_kernel(general if i % 2 else product)
+        K = (300.0, 300.0, (W - 1) / 2.0, (H - 1) / 2.0)
+        # more than 5 blocks of the wider tile per 2 CUs
+        blocks = -(-W // 128) * -(-H // 16)
+        B = torch.cuda.get_device_properties(0).multi_processor_count * 5 // 2 // blocks + 3
+        z = 2.0 + 0.001 * np.add.outer(np.arange(H), 0.7 * np.arange(W))
+        imgs = z + 1e-3 * rng.standard_normal((4, H, W))
+        imgs[1][rng.random((H, W)) < 0.01] = 0.0
+        imgs = (np.round(imgs * 1000).astype(np.uint16) if kind == "depth_u16"
+                else imgs.astype(np.float32))
+        pitch = W + pad
+        fs = H * pitch
+        store = torch.zeros(B * fs + 8, dtype=torch.from_numpy(imgs[:1]).dtype, device="cuda")
+        raw = store[skew:skew + B * fs].view(B, H, pitch)[:, :, :W]
+        four = torch.from_numpy(imgs).cuda()
+        for b in range(4):
+            for c in range(b, B, 4):
+                raw[c].copy_(four[b])
+        for agg, out in (("mean", "f32"), ("median", "f16")):
+            dt = sne.OUT_DTYPE[sne.OUT[out]]
+            label = "wide %d %s %dx%dx%d+%d/%d %s %s" % (n, kind, B, H, W, pad, skew, agg, out)
+            say("case", label)
+            nbuf = torch.full((3 * B * fs + 16,), 7.0, dtype=dt, device="cuda")
+            mbuf = torch.full((B * fs + 16,), 9, dtype=torch.uint8, device="cuda")
+            nv = nbuf[skew:skew + 3 * B * fs].view(B, 3, H, pitch)
+            mv = mbuf[skew:skew + B * fs].view(B, H, pitch)
+            sne.estimate_uniform(raw, K, kind, "custom", agg, out, normals=nv[..., :W],
+                                 mask=mv[..., :W], ctx=ctx)
+            torch.cuda.synchronize()
+            assert (nv[..., W:] == 7).all() and (mv[..., W:] == 9).all(), label
+            assert (nbuf[:skew] == 7).all() and (nbuf[skew + 3 * B * fs:] == 7).all(), label
+            assert (mbuf[:skew] == 9).all() and (mbuf[skew + B * fs:] == 9).all(), label
+            bits = torch.int32 if out == "f32" else torch.int16
+            for b in range(4):
+                sn, sm = sne.estimate(raw[b], K, kind, "custom", agg, out, ctx=ctx)
+                torch.cuda.synchronize()
+                want = sn.view(bits)
+                got = nv[b::4, :, :, :W].contiguous().view(bits)
+                assert torch.equal(got, want.expand_as(got)), label
+                assert torch.equal(mv[b::4, :, :W], sm.expand_as(mv[b::4, :, :W])), label
