@@ -120,7 +120,7 @@ int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 // workloads (one frame of 101x103 to 64 of 480x640, every input kind, both
 // rules, several sets of buffers in turn).
 //
-// Small launches, up to about one round of wavefronts: a call's time is that of
+// Small launches, up to one or two rounds of wavefronts: a call's time is that of
 // one wavefront, which walks its rows one after the other, so the work goes to
 // as many wavefronts as help.  FP32 input: 1 column and 1 or 2 rows while they
 // make no more than 8 wavefronts per CU, then 2 columns, or 4 where FP16 output
@@ -177,6 +177,9 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
     const auto half_of = [&](int px) { return lanes(px, 1) < lanes(px, 0) ? 1 : 0; };
     const auto work = [&](int px, int half) { return lanes(px, half) * (40 + 60 * px); };
     const int widest = (v.kind & SNE_LENIENT) ? std::min(pxmax, 2) : pxmax;
+    // output rows of a width that is no multiple of 256 bytes, at any pitch
+    const bool cut = (int64_t)W * (int64_t)out_elem(v.out) % kRowAlign != 0;
+    const bool f32 = v.out == SNE_OUT_F32;
     if (!uneven) {
         const bool four = v.out == SNE_OUT_F16 && widest == 4 &&
                           work(4, half_of(4)) < work(2, half_of(2));
@@ -185,7 +188,7 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
         struct Step {
             int px, rows, aim, most;
         };
-        const Step fp32[] = {{1, 2, 8, 8}, {2, 2, 10, 10}, {four ? 4 : 2, 4, 20, 20}};
+        const Step fp32[] = {{1, 2, 8, 8}, {2, 2, 10, 10}, {four ? 4 : 2, 4, 20, cut ? 20 : 40}};
         const Step quantised[] = {{1, 5, 8, (v.kind & SNE_LENIENT) ? 60 : 40}};
         const bool q = in_elem(v.kind) == 2;
         for (const Step *s = q ? quantised : fp32; s != (q ? quantised + 1 : fp32 + 3); ++s) {
@@ -198,9 +201,6 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
             return t;
         }
     }
-    // output rows of a width that is no multiple of 256 bytes, at any pitch
-    const bool cut = (int64_t)W * (int64_t)out_elem(v.out) % kRowAlign != 0;
-    const bool f32 = v.out == SNE_OUT_F32;
     const bool light = in_elem(v.kind) == 4 && !(v.kind & SNE_LENIENT);
     const int64_t bytes = B * H * W * (int64_t)(in_elem(v.kind) + 3 * out_elem(v.out) + 1);
     const bool one_range = bytes <= (128 << 20) && !(cut && f32) && !(light && (cut || f32));
