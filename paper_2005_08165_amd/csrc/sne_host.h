@@ -18,8 +18,11 @@ namespace sne {
 
 constexpr int kVersion = 10500;  // 1.5.0
 // Tile-shape cache entries carry the version of the kernels they were timed
-// on; it changes only when the kernels' speed characteristics do.
-constexpr int kTileCacheVersion = 10200;
+// on; it changes only when the kernels' speed characteristics do.  Entries of
+// 10200 know at most the 1 or 2 columns that rows of odd width or alignment
+// could take then, and 4 columns for the lenient rule (128 dense 375x1242
+// disparity frames: 235-240 us in their shape, 212 in the present one).
+constexpr int kTileCacheVersion = 10500;
 constexpr int kChunkOrder = 16;     // the runs-of-G block order the tuner tries
 constexpr int kMaxChunkOrder = 1024;  // largest G a tuning table may name
 constexpr int kSlots = 4;        // in-flight uneven batches per context

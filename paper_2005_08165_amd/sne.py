@@ -26,7 +26,7 @@ SNE_OK = 0
 SNE_ERR_ARG, SNE_ERR_BUDGET, SNE_ERR_STATE = -1, -3, -5
 SNE_NOALLOC_MAX_FRAMES = 4096  # include/sne.h
 # version tag the library writes into (and requires of) tile-table entries
-TILE_CACHE_VERSION = 10200
+TILE_CACHE_VERSION = 10500
 STATUS = {0: "SNE_OK", -1: "SNE_ERR_ARG", -2: "SNE_ERR_UNSUPPORTED", -3: "SNE_ERR_BUDGET",
           -4: "SNE_ERR_HIP", -5: "SNE_ERR_STATE", -6: "SNE_ERR_FULL", -7: "SNE_ERR_IO"}
 

@@ -280,3 +280,10 @@ def test_default_tile_spreads_small_launches(B, H, W, kind):
     bands = -(-H // t.rows)
     waves = B * strips * (-(-bands // 2) if t.lanes == 32 else bands)
     assert waves >= min(1024, B * H * -(-W // 64)), (t.cols_per_lane, t.rows, t.lanes, waves)
+
+
+def test_tile_cache_version_is_newer_than_the_narrow_kernels():
+    """Tables saved when rows of odd width or alignment took one or two columns
+    per lane, and lenient ones four, carry version 10200; their entries would
+    override shapes that are faster now."""
+    assert sne.TILE_CACHE_VERSION > 10200

@@ -494,6 +494,44 @@ def test_block_orders_bitwise(tmp_path):
             assert torch.equal(m, ref[1]), order
 
 
+def test_table_rows_of_another_version_are_dropped(tmp_path):
+    """sne_autotune_load takes a row of this library's tile-cache version and
+    ignores the same row of another one."""
+    arch, path = _table_arch(), str(tmp_path / "t.txt")
+    plain = sne.Context(0, tuning=False).get_tile(375, 1242, 128, "disparity_f32", "scharr",
+                                                  "median", "f32")
+    for version, want in ((10200, plain), (sne.TILE_CACHE_VERSION + 1, plain),
+                          (sne.TILE_CACHE_VERSION, (1, 7, 32))):
+        with open(path, "w") as f:
+            f.write("%s %d 375 1242 2 %d %d %d 0 0 1 7 0 1\n" % (
+                arch, version, sne.KIND["disparity_f32"], sne.GRAD["scharr"], sne.AGG["median"]))
+        ctx = sne.Context(0, tuning=False)
+        ctx.autotune_load(path)
+        assert ctx.get_tile(375, 1242, 128, "disparity_f32", "scharr", "median", "f32") == want
+
+
+def test_shipped_table_reaches_the_context():
+    """Every row of the shipped table for this GPU is the shape a context
+    created with it uses."""
+    ctx = sne.Context(0)
+    arch, rows = _table_arch(), 0
+    names = [{v: k for k, v in t.items()} for t in (sne.KIND, sne.GRAD, sne.AGG, sne.OUT)]
+    for line in open(sne.TUNING_TABLE):
+        f = line.split()
+        if line.startswith("#") or f[0] != arch:
+            continue
+        H, W, bc, kind, grad, agg, out, layout, px, height, _, half = map(int, f[2:])
+        if bc == 3:  # uneven batches have no lookup by size
+            continue
+        kind, grad, agg, out = (n[v] for n, v in zip(names, (kind, grad, agg, out)))
+        pin = sne.row_pitch(W, sne.KIND_DTYPE[sne.KIND[kind]]) if layout else W
+        pout = sne.row_pitch(W, sne.OUT_DTYPE[sne.OUT[out]]) if layout else W
+        assert ctx.get_tile(H, W, (1, 8, 64)[bc], kind, grad, agg, out, in_pitch=pin,
+                            out_pitch=pout) == (px, height, 32 if half else 64), line
+        rows += 1
+    assert rows > 0
+
+
 def test_autotune_and_tuning_table():
     """The autotuner returns a valid shape that the context then uses; a
     context created with the shipped table reports the table's entry for the
