@@ -914,7 +914,8 @@ int sne_get_tile_pitched(sne_ctx *ctx, int32_t H, int32_t W, int32_t B, int64_t 
     const int64_t ir = in_pitch * (int64_t)in_elem(kind);
     const int64_t orow = out_pitch * (int64_t)out_elem(out_type);
     const int layout = row_layout(base, ir, ir * H) && row_layout(base, orow, 3 * orow * H);
-    report_tile(pick_tile(ctx, H, W, B, v, 4, false, layout), tile);
+    const int pxmax = max_px(base, base, W, kind, out_type);
+    report_tile(pick_tile(ctx, H, W, B, v, pxmax, false, layout), tile);
     return SNE_OK;
 }
 

@@ -89,3 +89,12 @@ def test_pitched_autotune_records_the_padded_class():
                          ctx=ctx)
     torch.cuda.synchronize()
     assert torch.equal(nd, nrm) and torch.equal(md, msk)
+
+
+def test_forced_columns_of_a_narrow_frame_are_reported():
+    """A frame narrower than the forced columns per lane takes fewer, and
+    sne_get_tile says so."""
+    ctx = sne.Context(0, tuning=False)
+    ctx.set_tile(4, 6, 32)
+    for W, cols in ((1, 1), (2, 2), (3, 2), (4, 4), (5, 4)):
+        assert ctx.get_tile(9, W, 1, "depth_f32", "fd", "mean", "f32") == (cols, 6, 32), W
