@@ -658,7 +658,8 @@ __device__ __forceinline__ float slot_sum(float Gu, float Gv, const float (&rj)[
     }
 }
 
-// B + the mean of the kept candidates.  1/8 is exact and v_rcp_f32 returns it
+// B + the mean of the kept candidates, strict rule (lenient means take the pair
+// form, kPairMean).  1/8 is exact and v_rcp_f32 returns it
 // exactly for m = 8, so a pixel with nothing left out gets the same bits
 // whichever path its wavefront takes.  With nothing kept the sum is 0 and
 // 0 * (1/0) is NaN, which the caller's norm test turns into the degenerate
@@ -668,7 +669,7 @@ __device__ __forceinline__ float finish_mean(float sum, float weight, float zc, 
     if constexpr (KIND == KIND_DISP) return fmaf(-(sum * zc), weight, B);
     return fmaf(sum, weight, B);
 }
-template <int KIND, bool LEN>
+template <int KIND>
 __device__ __forceinline__ float mean8(float Gu, float Gv, const float (&rj)[8],
                                        const float (&zj)[8], float zc,
                                        float B, bool general) {
@@ -677,7 +678,7 @@ __device__ __forceinline__ float mean8(float Gu, float Gv, const float (&rj)[8],
     int m = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const bool drop = left_out<LEN>(zj[j], zc);
+        const bool drop = left_out<false>(zj[j], zc);
         r[j] = drop ? 0.f : rj[j];
         m += drop ? 0 : 1;
     }
@@ -831,7 +832,7 @@ __device__ __forceinline__ float normal_z(int k, const FrameDesc &f, int col, fl
         }
         return finish_mean<KIND>(sum, rcp((float)m), zc, B);
     } else if constexpr (AGG == AGG_MEAN) {
-        return mean8<KIND, LEN>(Gu, Gv, rj, zj, zc, B, GENERAL);
+        return mean8<KIND>(Gu, Gv, rj, zj, zc, B, GENERAL);
     } else {
         const float Spp = Gu + Gv, Spm = Gu - Gv;
         const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};
@@ -1553,7 +1554,7 @@ __global__ __launch_bounds__(kBlock) void sne_wide_kernel(WideArgs a) {
             }
             float nz;
             if constexpr (AGG == AGG_MEAN) {
-                nz = mean8<KIND, false>(Gu, Gv, rj, zj, z0, B, general);
+                nz = mean8<KIND>(Gu, Gv, rj, zj, z0, B, general);
             } else {
                 const float Spp = Gu + Gv, Spm = Gu - Gv;
                 const float Nj[8] = {Gu, -Gu, Gv, -Gv, Spp, -Spp, -Spm, Spm};

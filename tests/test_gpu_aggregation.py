@@ -166,3 +166,40 @@ def test_single_ties_at_every_column_fp32(kind):
         on, om = oracle.estimate(img, ORACLE_KIND[kind], k32(K), "fd", "mean")
         check_parity(n.double().cpu().numpy(), m.cpu().numpy(), on, om, out,
                      label="%s %s" % (kind, out))
+
+
+@pytest.mark.parametrize("out", ["f32", "f16"])
+@pytest.mark.parametrize("kind", ["depth_f32+lenient", "depth_u16+lenient"] + list(DTYPE))
+def test_any_width_and_alignment_bitwise_mean(kind, out):
+    """As test_any_width_and_alignment_bitwise, for the means, which count
+    their candidates in other ways than the medians."""
+    base = kind.partition("+")[0]
+    H, K = 9, (400.0, 400.0, 255.5, 4.0)
+    dt = sne.OUT_DTYPE[sne.OUT[out]]
+    ctx = sne.Context(0, tuning=False)
+    for W, pad, skew in ((1, 0, 0), (3, 2, 1), (5, 0, 3), (127, 0, 1), (257, 3, 0), (258, 0, 1),
+                         (259, 1, 2)):
+        img = torch.from_numpy(_noisy(base, H, W)).cuda()
+        pitch = W + pad
+        store = torch.zeros(H * pitch + 8, dtype=img.dtype, device="cuda")
+        raw = store[skew:skew + H * pitch].view(H, pitch)[:, :W]
+        raw.copy_(img)
+        ref = None
+        for px, rows, lanes in ((1, 3, 64), (2, 2, 64), (2, 3, 32), (4, 4, 64), (4, 2, 32)):
+            ctx.set_tile(px, rows, lanes)
+            nbuf = torch.full((3 * H * pitch + 16,), 7.0, dtype=dt, device="cuda")
+            mbuf = torch.full((H * pitch + 16,), 9, dtype=torch.uint8, device="cuda")
+            n = nbuf[skew:skew + 3 * H * pitch].view(3, H, pitch)
+            m = mbuf[skew:skew + H * pitch].view(H, pitch)
+            sne.estimate(raw, K, kind, "fd", "mean", out, normals=n[..., :W], mask=m[:, :W],
+                         ctx=ctx)
+            got = (nbuf.cpu().view(torch.int32 if out == "f32" else torch.int16), mbuf.cpu())
+            if ref is None:
+                ref = got
+                on, om = oracle.estimate(img.cpu().numpy(), ORACLE_KIND[base], k32(K), "fd",
+                                         "mean", rule="lenient" if "+" in kind else "strict")
+                check_parity(n[..., :W].double().cpu().numpy(), m[:, :W].cpu().numpy(), on, om,
+                             out, "%s mean W=%d" % (kind, W))
+                assert (n[..., W:] == 7).all() and (m[:, W:] == 9).all()
+            for a, b in zip(ref, got):
+                assert torch.equal(a, b), (kind, out, W, pad, skew, px, rows, lanes)
