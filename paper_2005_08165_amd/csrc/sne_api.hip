@@ -136,7 +136,9 @@ int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 // frame.  A lane's row costs about 40 + 60 px instructions whatever its columns
 // hold; half waves cost 5 % more, and at widths that are no multiple of their
 // 4-column vectors 30 % with FP32 output (20 x 1001x1333 Scharr-median: 133 us
-// in half waves, 98 in full ones) and 10 % with FP16.  The lenient rule's
+// in half waves, 98 in full ones) and 10 % with FP16 (30 % in uneven batches:
+// 64 frames up to 700x900, disparity FD-mean, 60 us in full waves, 70 in half
+// ones).  The lenient rule's
 // kernels hold so many registers at 4 columns that 2 are faster (64 x 480x640
 // Sobel-median: 87 against 101 us).
 //
@@ -150,8 +152,12 @@ int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 // 82; Sobel-median 83, 75, 81).  16-bit input wants the taller tile (20 x
 // 1001x1333 u16 Sobel-median, padded: 2 rows 108 us, 4 rows 99).  The shape is
 // 5 % slower than the best of such a workload on average, 28 % at most.
-// Uneven batches: 20 rows (the persistent kernel finds a frame per tile) if
-// that leaves enough tiles.
+// Uneven batches: 20 rows if that leaves enough tiles, at least 4 (2 for a small
+// image or two): the
+// persistent kernel takes a tile from a queue, finds its frame and reads its
+// tables first (2 FP32 frames up to 1080x1920, FD-mean: 4 x 10 rows 27 us, 3 rows
+// 38).  The lenient rule on FP32 depth is faster at 4 columns there (64 frames
+// FD-mean 158 us, 176 at 2), on 16-bit depth at 2 as elsewhere.
 //
 // Block order: one range of tiles per XCD for small launches (the halo rows of
 // neighbouring tiles then meet in that XCD's L2: 5 % less time than runs of
@@ -169,14 +175,16 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
     const auto lanes = [&](int px, int half) {  // what a row of the frame takes
         const TileChoice t{px, 1, kChunkOrder, half};
         return (double)tile_nstrips(W, t) * (half ? 32 : 64) *
-               (!half ? 1.0 : W % 4 == 0 ? 1.05 : v.out == SNE_OUT_F32 ? 1.3 : 1.1);
+               (!half ? 1.0 : W % 4 == 0 ? 1.05 : v.out == SNE_OUT_F32 || uneven ? 1.3 : 1.1);
     };
     const auto waves = [&](const TileChoice &t) {  // of tiles of 1 row
         return B * H * tile_nstrips(W, t) / (t.half ? 2 : 1);
     };
     const auto half_of = [&](int px) { return lanes(px, 1) < lanes(px, 0) ? 1 : 0; };
     const auto work = [&](int px, int half) { return lanes(px, half) * (40 + 60 * px); };
-    const int widest = (v.kind & SNE_LENIENT) ? std::min(pxmax, 2) : pxmax;
+    const bool f32in = in_elem(v.kind) == 4;
+    const int widest =
+        (v.kind & SNE_LENIENT) && !(uneven && f32in) ? std::min(pxmax, 2) : pxmax;
     // output rows of a width that is no multiple of 256 bytes, at any pitch
     const bool cut = (int64_t)W * (int64_t)out_elem(v.out) % kRowAlign != 0;
     const bool f32 = v.out == SNE_OUT_F32;
@@ -190,8 +198,8 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
         };
         const Step fp32[] = {{1, 2, 8, 8}, {2, 2, 10, 10}, {four ? 4 : 2, 4, 20, cut ? 20 : 40}};
         const Step quantised[] = {{1, 5, 8, (v.kind & SNE_LENIENT) ? 60 : 40}};
-        const bool q = in_elem(v.kind) == 2;
-        for (const Step *s = q ? quantised : fp32; s != (q ? quantised + 1 : fp32 + 3); ++s) {
+        for (const Step *s = f32in ? fp32 : quantised; s != (f32in ? fp32 + 3 : quantised + 1);
+             ++s) {
             if (s->px > pxmax) continue;
             TileChoice t{s->px, s->rows, 1, half_of(s->px)};
             const int64_t w = waves(t);
@@ -201,7 +209,7 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
             return t;
         }
     }
-    const bool light = in_elem(v.kind) == 4 && !(v.kind & SNE_LENIENT);
+    const bool light = f32in && !(v.kind & SNE_LENIENT);
     const int64_t bytes = B * H * W * (int64_t)(in_elem(v.kind) + 3 * out_elem(v.out) + 1);
     const bool one_range = bytes <= (128 << 20) && !(cut && f32) && !(light && (cut || f32));
     const int order = one_range ? 1 : kChunkOrder;
@@ -219,7 +227,8 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
     }
     const int64_t full = cu * 16;  // wavefronts, 4 per SIMD, are resident
     if (uneven) {
-        best.rows = (int)std::min<int64_t>(std::max<int64_t>(waves(best) / full, 2), 20);
+        best.rows = (int)std::min<int64_t>(
+            std::max<int64_t>(waves(best) / full, waves(best) < full ? 2 : 4), 20);
         return best;
     }
     best.rows = 8;
