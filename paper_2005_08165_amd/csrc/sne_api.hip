@@ -125,7 +125,9 @@ int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 // as many wavefronts as help.  FP32 input: 1 column and 1 or 2 rows while they
 // make no more than 8 wavefronts per CU, then 2 columns, or 4 where FP16 output
 // makes their stores 8 bytes and no lanes are wasted.  16-bit input, bound by
-// instruction issue: 1 column throughout.  One frame's kernel, against half
+// instruction issue: 1 column by up to 5 rows, longer under the lenient rule and
+// where 4 columns would idle lanes (8 x 427x561 f16 Sobel-median 12 % less time;
+// one 1080x1920 frame 4 % more).  One frame's kernel, against half
 // waves or 4 columns by 4 rows: 101x103 FP32 FD-mean 3.0 us (5.0), 240x320
 // Sobel-median 3.0 (5.3), 480x640 FD-mean 3.8 (6.0), u16 FD-median 4.1 (6.8),
 // 375x1242 Sobel-median 4.7 (8.0); 4 frames of 480x640 6.7 (8.4), 8 of them 9.8
@@ -138,25 +140,26 @@ int batch_class(int64_t B) { return B <= 1 ? 0 : (B <= 8 ? 1 : 2); }
 // 4-column vectors 30 % with FP32 output (20 x 1001x1333 Scharr-median: 133 us
 // in half waves, 98 in full ones) and 10 % with FP16 (30 % in uneven batches:
 // 64 frames up to 700x900, disparity FD-mean, 60 us in full waves, 70 in half
-// ones).  The lenient rule's
-// kernels hold so many registers at 4 columns that 2 are faster (64 x 480x640
-// Sobel-median: 87 against 101 us).
+// ones).  The lenient rule's kernels hold so many registers at 4 columns that 2
+// are faster (64 x 480x640 Sobel-median: 87 against 101 us).
 //
 // Rows: 8 where there are enough tiles for it, 4 otherwise (the first row of
 // a tile costs about two); FP32 output of a width that is no multiple of 256
-// bytes, at any pitch: 4, or 2 in large batches of FP32 input.  With dense rows
+// bytes, at any pitch: 4, or 2 in large batches that HBM bounds.  With dense rows
 // neighbouring strips share a cache line, which their wavefronts should write at
 // about the same time (40 x 500x1242 disparity Sobel-median: 2 rows 91 us, 4
 // rows 102, 8 rows 109).  Padded rows have no such lines and no height that is
 // best for all (same batch, FP32 depth: FD-mean 2 rows 67 us, 4 rows 76, 8 rows
-// 82; Sobel-median 83, 75, 81).  16-bit input wants the taller tile (20 x
-// 1001x1333 u16 Sobel-median, padded: 2 rows 108 us, 4 rows 99).  The shape is
-// 5 % slower than the best of such a workload on average, 28 % at most.
+// 82; Sobel-median 83, 75, 81).  Medians of 16-bit input after a 3-row filter are
+// bound by issue (20 x 1001x1333 u16 Sobel-median, padded: 2 rows 108 us, 4 rows
+// 99), other filters are not (40 x 500x1242 u16, dense: FD-mean 80 and 100,
+// FD-median 89 and 97).  The shape is 5 % slower than the best of such a workload
+// on average, 28 % at most.
+//
 // Uneven batches: 20 rows if that leaves enough tiles, at least 4 (2 for a small
-// image or two): the
-// persistent kernel takes a tile from a queue, finds its frame and reads its
-// tables first (2 FP32 frames up to 1080x1920, FD-mean: 4 x 10 rows 27 us, 3 rows
-// 38).  The lenient rule on FP32 depth is faster at 4 columns there (64 frames
+// image or two): the persistent kernel takes a tile from a queue, finds its frame
+// and reads its tables first (2 FP32 frames up to 1080x1920, FD-mean: 4 x 10 rows
+// 27 us, 3 rows 38).  The lenient rule on FP32 depth is faster at 4 columns there (64 frames
 // FD-mean 158 us, 176 at 2), on 16-bit depth at 2 as elsewhere.
 //
 // Block order: one range of tiles per XCD for small launches (the halo rows of
@@ -197,7 +200,8 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
             int px, rows, aim, most;
         };
         const Step fp32[] = {{1, 2, 8, 8}, {2, 2, 10, 10}, {four ? 4 : 2, 4, 20, cut ? 20 : 40}};
-        const Step quantised[] = {{1, 5, 8, (v.kind & SNE_LENIENT) ? 60 : 40}};
+        const bool idle = work(1, half_of(1)) < 1.25 * work(4, half_of(4));  // lanes, at 4
+        const Step quantised[] = {{1, 5, 8, (v.kind & SNE_LENIENT) ? 60 : idle ? 40 : 22}};
         for (const Step *s = f32in ? fp32 : quantised; s != (f32in ? fp32 + 3 : quantised + 1);
              ++s) {
             if (s->px > pxmax) continue;
@@ -211,7 +215,7 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
     }
     const bool light = f32in && !(v.kind & SNE_LENIENT);
     const int64_t bytes = B * H * W * (int64_t)(in_elem(v.kind) + 3 * out_elem(v.out) + 1);
-    const bool one_range = bytes <= (128 << 20) && !(cut && f32) && !(light && (cut || f32));
+    const bool one_range = bytes <= (96 << 20) && !(cut && f32) && !(light && (cut || f32));
     const int order = one_range ? 1 : kChunkOrder;
     TileChoice best{1, 4, order, 0};
     double best_cost = 0.0;
@@ -232,7 +236,9 @@ TileChoice default_tile(const sne_ctx *ctx, int H, int W, int64_t B, int pxmax, 
         return best;
     }
     best.rows = 8;
-    if (cut && f32) best.rows = light && B * H * W > (16 << 20) ? 2 : 4;
+    const bool slow = (v.kind & SNE_LENIENT) ||
+                      (!f32in && v.agg == SNE_AGG_MEDIAN && v.grad != SNE_GRAD_FD);
+    if (cut && f32) best.rows = !slow && B * H * W > (16 << 20) ? 2 : 4;
     if (best.rows == 8 && waves(best) / 8 < full * 9 / 10) best.rows = 4;
     return best;
 }
