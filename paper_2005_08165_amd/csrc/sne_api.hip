@@ -635,10 +635,13 @@ std::vector<TileChoice> tile_candidates(int H, int pxmax, bool remap_choices) {
 // the eight fastest are then timed again with 8 ms bursts in interleaved
 // rounds, so that a slow phase of the device does not favour whichever
 // candidate ran during it, and the best median wins.  `launch` enqueues one
-// launch of a shape on `st`.  Returns rows = 0 if nothing could be timed.
-TileChoice pick_fastest(const std::vector<TileChoice> &cand, const TileChoice &probe,
+// launch of a shape on `st`.  `probe`, the shape used without tuning, is a
+// candidate too (the rule's shapes for small launches have 1 or 3 rows).
+// Returns rows = 0 if nothing could be timed.
+TileChoice pick_fastest(std::vector<TileChoice> cand, const TileChoice &probe,
                         const std::function<bool(const TileChoice &)> &launch, hipStream_t st,
                         hipEvent_t e0, hipEvent_t e1) {
+    cand.push_back(probe);
     int burst = 3;
     auto time_one = [&](const TileChoice &t, float &ms) -> bool {
         if (!launch(t)) return false;  // warm-up
