@@ -204,9 +204,10 @@ template <> struct Raw<KIND_F16> {
 // select per pixel for the three channels (mul_or_zero) and the middle row's
 // pairs formed last, this took the 4-column FP32 Sobel-median kernel from
 // 127 to 114 registers and 48 to 40 half-rate instructions per pixel:
-// 64 x 480x640 in 57.6 instead of 60.4 us (5.8 TB/s of algorithmic bytes,
-// about what the plain streams of its access pattern reach), 1024 uneven u16
-// frames FD-mean in 1.91 instead of 2.0 ms.
+// 64 x 480x640 in 57.6 instead of 60.4 us with the input in the last-level
+// cache (5.8 TB/s of algorithmic bytes, 0.94 of the rate of a kernel of the same
+// streams without arithmetic; 68 us, 0.79 of it, where the input comes from HBM),
+// 1024 uneven u16 frames FD-mean in 1.91 instead of 2.0 ms.
 using Mask = uint64_t;
 __device__ __forceinline__ Mask mask_of(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 __device__ __forceinline__ bool lane(Mask m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
@@ -1000,8 +1001,8 @@ __device__ __forceinline__ void tile_row(const FrameDesc &f, const InBuf &ib, co
             // For the mean, a class test of the plain sum says the same in one
             // half-rate instruction instead of five, but a pixel with ties
             // then forms both sums: 64 x 480x640 FD-mean, FP16 output, 42.6
-            // instead of 42.9 us on depth without ties, 57.0 instead of 51.1
-            // on millimetres converted to metres.
+            // instead of 42.9 us on depth without ties (1-3 % in 48 forms), 57.0
+            // instead of 51.1 on millimetres converted to metres (6 %, at most 13).
             if constexpr (!kTieHeavy<KIND> && !kPairMean<KIND, AGG, LEN>) {
                 const int c = k + 1;
                 const float rmax = vmax8abs(rc.rE[c], rc.rE[c - 1], pd.rS[k], pu.rS[k], pd.rSE[c],
